@@ -1,0 +1,102 @@
+"""GPU parity of single kernel paths at the sizes where they can go wrong
+(tile edges, remainders, the smallest and largest of a path's range), against
+the float64 oracle at the tolerances of tests/parity.py."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_11232_amd import synth
+from tests.parity import run_parity, say
+
+pytestmark = pytest.mark.gpu
+
+
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def launch_workload(cfg, q_lens, lens, seed, prefix=0):
+    """One launch of sequences of lens[i] tokens whose last q_lens[i] are
+    queried; the first ``prefix`` (whole blocks) are one cached prefix."""
+    r = np.random.default_rng(seed)
+    Val, bs = synth.Values, cfg.block_size
+    kv = (cfg.num_kv_heads, cfg.head_dim)
+
+    def values(tag, *shape):
+        return Val((cfg.seed, seed) + tag, shape, cfg.dtype)
+
+    pt = r.integers(0, 1 << 17, size=prefix).astype(np.int32)
+    setup, pre = [], []
+    if prefix:
+        sid = synth.PREFIX_SEQ_BASE
+        setup += [synth.Op("add", sid, pt),
+                  synth.Op("write_kv", sid, k=values((1,), prefix, *kv),
+                           v=values((2,), prefix, *kv)), synth.Op("free", sid)]
+    for i, (q, L) in enumerate(zip(q_lens, lens)):
+        toks = np.concatenate([pt, r.integers(0, 1 << 17, size=L - prefix).astype(np.int32)])
+        own = L - q - prefix  # cached tokens of the sequence's own
+        if own > 0:
+            setup += [synth.Op("add", i, toks[:L - q]),
+                      synth.Op("write_kv", i, k=values((3, i), own, *kv),
+                               v=values((4, i), own, *kv))]
+            pre.append(synth.Op("extend", i, toks[L - q:]))
+        else:
+            pre.append(synth.Op("add", i, toks))
+    T = sum(q_lens)
+    launch = synth.Launch(pre, list(range(len(lens))), list(q_lens),
+                          values((5,), T, cfg.num_q_heads, cfg.head_dim),
+                          values((6,), T, *kv), values((7,), T, *kv))
+    nb = sum(-(-x // bs) for x in lens) + prefix // bs + 8
+    return synth.Workload(cfg, nb, np.random.default_rng(seed).permutation(nb).astype(np.int32),
+                          setup, [launch], None, -(-max(lens) // bs))
+
+
+# (q heads, kv heads, head_dim, query tokens, lengths): 16- and 32-row
+# workgroups (the latter from 512 of them), partial last tiles, group sizes
+# that do not divide a tile and ones above it, sequences of one token and of
+# none, more wavefronts than blocks, more sequences than one round of the
+# sequence search probes, a table of more than 64 blocks per wavefront
+F32 = [
+    (4, 4, 64, [1], [1]),
+    (8, 2, 64, [0, 7, 0, 5, 1], [4, 7, 33, 16, 300]),
+    (6, 2, 128, [17, 33], [40, 33]),
+    (40, 1, 64, [3, 1], [20, 129]),
+    (16, 2, 128, [1] * 70, [3 + 2 * i for i in range(70)]),
+    (8, 2, 128, [2, 1], [4200, 4097]),
+    (32, 32, 64, [520, 9], [600, 31]),
+    (32, 8, 128, [300, 230, 0], [317, 530, 64]),
+]
+
+
+@pytest.mark.parametrize("case", range(len(F32)))
+def test_f32_tiles(case):
+    _gpu()
+    hq, hkv, d, q_lens, lens = F32[case]
+    cfg = synth.AttnConfig(f"f32-{case}", "f32", hq, hkv, d, 16, 6100 + case)
+    errs, _, _ = run_parity(launch_workload(cfg, q_lens, lens, 40 + case), label=cfg.name)
+    say(f"{cfg.name} normalized errors", errs)
+
+
+def test_f32_values_that_are_not_finite_stay_with_their_rows():
+    """A new token's infinite or NaN values reach that token's row and later
+    ones, in those dimensions, and no earlier row of the same tile."""
+    _gpu()
+    from paper_2605_11232_amd.runtime import DeviceReplay
+    cfg = synth.AttnConfig("f32-inf", "f32", 4, 2, 64, 16, 6190)
+    wl = launch_workload(cfg, [20], [52], 77)
+    dev = DeviceReplay(wl).setup()
+    p = dev.prepare(wl.launches[0])
+    dev.append(p)
+    dev.attend(p)
+    plain = p.out.clone()
+    bad = 13
+    p.v_new[bad, :, 5], p.v_new[bad, :, 9] = float("inf"), float("nan")
+    dev.append(p)
+    dev.attend(p)
+    torch.cuda.synchronize()
+    assert torch.equal(p.out[:bad], plain[:bad])
+    dims = [i for i in range(cfg.head_dim) if i not in (5, 9)]
+    # same products in the same order
+    assert torch.equal(p.out[:, :, dims], plain[:, :, dims])
+    assert torch.isposinf(p.out[bad:, :, 5]).all() and torch.isnan(p.out[bad:, :, 9]).all()
