@@ -50,6 +50,11 @@ constexpr int kXcds = 8;
 constexpr int64_t kRowWavesPerCu = 10;      // row-item split target
 constexpr int64_t kPrivateTileKeys = 4160;  // most private keys a few-row tile item covers
 constexpr int64_t kMinRowKeys = 256;        // split target floor of row items
+// Fewest keys a row item is split down to in a launch without long sequences'
+// tiles (beside those the rows are not what it waits for), while the sequence's
+// part count stays within the workspace bound: 4 decode requests on a
+// 2048-token prefix 19.4 us per append and call against 20.7 with 256 (128: even).
+constexpr int64_t kPlanRowKeys = 192;
 constexpr int64_t kTailWorkPct = 10;        // row work given half-length items (per cent)
 constexpr int64_t kStealPct = 5;            // tile work in the tail list (per cent)
 
@@ -264,7 +269,6 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
         }
         cg_begin.push_back(int32_t(cg_seqs.size()));
         cg_keys.push_back(int32_t(S));
-        cg_chunks.push_back(int32_t(cdiv(S, pa::kSharedChunk)));
       }
     }
 
@@ -273,20 +277,25 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
     // CU busy, a split target of at least kMinRowKeys and at most 1024 keys
     // per item (halved for the tail below).
     int64_t row_keys = 0;
-    for (int32_t r = 0; r < n_seqs; ++r)
+    bool long_seqs = false;
+    for (int32_t r = 0; r < n_seqs; ++r) {
       if (is_row(r) && !on_tiles(r))
         row_keys += int64_t(seq_lens[r] - kstart[r]) * num_kv_heads;
+      long_seqs = long_seqs || (qlen(r) > 0 && !is_row(r));
+    }
     const int64_t target_waves = int64_t(num_cus) * kRowWavesPerCu;
-    int64_t chunk = std::max<int64_t>(kMinRowKeys, cdiv(row_keys, std::max<int64_t>(1, target_waves)));
-    chunk = cdiv(chunk, pa::kKeyStep) * pa::kKeyStep;
-    // a row item's block ids fit one wavefront (64 lanes): at most 1024 keys
-    chunk = std::min<int64_t>(chunk, int64_t(pa::kRowItemBlocks) * block_size);
     // The sequences with the fewest private keys, up to kTailWork of the row
     // work, get half-length items: ordered longest first, those run last, so
     // the launch drains sooner.  A sequence keeps at most cdiv(L, kMinRowKeys)
     // private parts (the workspace bound).
-    std::vector<int64_t> row_chunk(n_seqs, chunk);
-    if (row_keys > 0) {
+    std::vector<int64_t> row_chunk;
+    auto split_rows = [&](int64_t least) {
+      int64_t chunk = std::max<int64_t>(least, cdiv(row_keys, std::max<int64_t>(1, target_waves)));
+      chunk = cdiv(chunk, pa::kKeyStep) * pa::kKeyStep;
+      // a row item's block ids fit one wavefront (64 lanes): at most 1024 keys
+      chunk = std::min<int64_t>(chunk, int64_t(pa::kRowItemBlocks) * block_size);
+      row_chunk.assign(n_seqs, chunk);
+      if (row_keys == 0) return;
       std::vector<std::pair<int64_t, int32_t>> by_len;
       for (int32_t r = 0; r < n_seqs; ++r)
         if (is_row(r) && !on_tiles(r)) by_len.push_back({int64_t(seq_lens[r] - kstart[r]), r});
@@ -298,8 +307,68 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
         if (acc > row_keys * kTailWorkPct / 100) break;
         if (cdiv(len, half) <= cdiv(seq_lens[r], kMinRowKeys)) row_chunk[r] = half;
       }
-    }
+    };
+    // private parts of a sequence, within the workspace bound's part count
+    auto private_parts = [&](int32_t r) {
+      const int64_t L = seq_lens[r], len = L - kstart[r];
+      const int64_t most = cdiv(L, kMinRowKeys) + (L > pa::kSharedMinKeys ? cdiv(L, pa::kSharedChunk) : 0) -
+                           (cgroup[r] >= 0 ? cg_chunks[cgroup[r]] : 0);
+      return std::max<int64_t>(1, std::min(cdiv(len, on_tiles(r) ? kPrivateTileKeys : row_chunk[r]), most));
+    };
+    for (int32_t S : cg_keys) cg_chunks.push_back(int32_t(cdiv(S, pa::kSharedChunk)));
+    split_rows(long_seqs ? kMinRowKeys : kPlanRowKeys);
 
+    // Key chunks of the shared prefixes.  A shared item is a serial walk over
+    // its keys, so in a launch with little else to do few long chunks leave
+    // the chip waiting for them.  Chunks are cut until an item takes a third of
+    // what the rest of the launch takes (its steps run slower beside that; kStep*:
+    // what the whole chip does during one 64-key step) or about as long as the
+    // longest private item (a row item's 32-key step takes about as long as
+    // 64 keys of a tile), as long as every chunk still starts at once, one
+    // workgroup per CU.  Append and call, us, whole and cut: 4 decode requests of
+    // 256-1152 keys of their own on a 2048-token prefix, 32/8 heads, 42 and 19; 64 of
+    // them 65 and 48; 128 on 8192 tokens 119 and 85; 64 of 100-300 on 8192,
+    // 28/4 heads, 84 and 32; 16 verifications of 5 tokens on 4096 84 and 34.  A half
+    // or a sixth instead of a third: up to 12 % slower.  256 decode requests have
+    // enough private work (143 us, one chunk either way).
+    if (!cg_keys.empty()) {
+      constexpr double kStepBytes = 6.6e6, kStepFlops = 1.2e9;  // 1.2 us at 5.5 TB/s, 1 PFLOP/s
+      double rest = 0;      // steps
+      int64_t longest = 0;  // keys, in tile steps
+      for (int32_t r = 0; r < n_seqs; ++r) {
+        if (qlen(r) == 0) continue;
+        const int64_t keys = seq_lens[r] - kstart[r];
+        if (is_row(r)) {
+          rest += double(keys) * num_kv_heads * head_dim * 4 / kStepBytes;
+          longest = std::max(longest, (on_tiles(r) ? 1 : 2) * cdiv(keys, private_parts(r)));
+        } else {
+          rest += 4.0 * head_dim * qlen(r) * num_q_heads * double(keys) / kStepFlops;
+        }
+      }
+      int64_t row_tiles = 0;
+      for (size_t c = 0; c < cg_keys.size(); ++c) {
+        const int64_t members = cg_begin[c + 1] - cg_begin[c];
+        row_tiles += cdiv(members * qlen(cg_seqs[cg_begin[c]]) * G, pa::kTileRows);
+      }
+      longest = std::max<int64_t>(longest, pa::kSharedMinKeys);
+      const int64_t third = 1 + int64_t(std::min(rest, 1e6) / 3 * pa::kTileStep);
+      for (size_t c = 0; c < cg_keys.size(); ++c) {
+        const int64_t n = std::min<int64_t>({cg_keys[c] / longest, (cg_keys[c] + third / 2) / third,
+                                             num_cus / (row_tiles * num_kv_heads)});
+        cg_chunks[c] = int32_t(std::max<int64_t>(cg_chunks[c], n));
+      }
+    }
+    // A decode plan that fits pa_attn_decode_noalloc's array with the coarser
+    // splits keeps fitting it.
+    if (kind == PA_KIND_DECODE) {
+      int64_t parts = 0;  // times G rows, per kv-head
+      for (int32_t r = 0; r < n_seqs; ++r)
+        parts += private_parts(r) + (cgroup[r] >= 0 ? cg_chunks[cgroup[r]] : 0);
+      if (parts * num_q_heads * (head_dim + 1) * 4 > int64_t(PA_NOALLOC_WORKSPACE_BYTES)) {
+        for (size_t c = 0; c < cg_keys.size(); ++c) cg_chunks[c] = int32_t(cdiv(cg_keys[c], pa::kSharedChunk));
+        split_rows(kMinRowKeys);
+      }
+    }
     std::vector<int64_t> tile_cost, row_cost, shared_cost;
     // head-0 partial base of a cascade member's merge group
     std::vector<int32_t> member_base(cg_keys.empty() ? 0 : size_t(n_seqs), -1);
@@ -312,7 +381,7 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
         if (is_row(r) && on_tiles(r))
           nt += cdiv(seq_lens[r] - kstart[r], kPrivateTileKeys);
         else if (is_row(r))
-          nr += std::max<int64_t>(1, cdiv(seq_lens[r] - kstart[r], row_chunk[r]));
+          nr += private_parts(r);
         else
           nt += cdiv(int64_t(qlen(r)) * G, pa::kTileRows);
       }
@@ -330,15 +399,14 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
       if (is_row(r)) {
         const int32_t k0s = kstart[r];
         const bool tiled = on_tiles(r);
-        const int64_t split = tiled ? kPrivateTileKeys : row_chunk[r];
         const int64_t kstep = tiled ? pa::kTileStep : pa::kKeyStep;
-        const int32_t nsplit = static_cast<int32_t>(std::max<int64_t>(1, cdiv(L - k0s, split)));
+        // parts 0 .. first-1 are the shared prefix's key chunks
+        const int32_t first = cgroup[r] >= 0 ? cg_chunks[cgroup[r]] : 0;
+        const int32_t nsplit = static_cast<int32_t>(private_parts(r));
         // equal private key ranges, multiples of the key step, covering [k0s, L)
         const int64_t per = cdiv(cdiv(L - k0s, nsplit), kstep) * kstep;
         int32_t used = 0;
         while (used < nsplit && k0s + int64_t(used) * per < L) ++used;
-        // parts 0 .. first-1 are the shared prefix's key chunks
-        const int32_t first = cgroup[r] >= 0 ? cg_chunks[cgroup[r]] : 0;
         const int32_t parts = used + first;
         int64_t base = -1;
         if (parts > 1) {

@@ -62,9 +62,10 @@ def marshal_launch(launch):
 def plan_words_bound(cfg, n_seqs: int, total_q: int, max_blocks_per_seq: int) -> int:
     """Upper bound on the plan size of a launch of n_seqs sequences and
     total_q query tokens (tile items, key-split items of at least 256 keys,
-    merge groups, cascade member tables, per-XCD padding)."""
+    merge groups, cascade member tables, per-XCD padding; in a small launch
+    the shared-prefix chunks that fill the chip)."""
     max_keys = max_blocks_per_seq * cfg.block_size
-    return 32 + 8 * (cfg.num_kv_heads * (total_q * cfg.group // 128 + n_seqs)
+    return 16384 + 32 + 8 * (cfg.num_kv_heads * (total_q * cfg.group // 128 + n_seqs)
                      + 2 * cfg.num_kv_heads * n_seqs * (max_keys // 256 + 2) + 64)
 
 

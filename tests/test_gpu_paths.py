@@ -100,3 +100,31 @@ def test_f32_values_that_are_not_finite_stay_with_their_rows():
     # same products in the same order
     assert torch.equal(p.out[:, :, dims], plain[:, :, dims])
     assert torch.isposinf(p.out[bad:, :, 5]).all() and torch.isnan(p.out[bad:, :, 9]).all()
+
+
+# (kind, q heads, kv heads, head_dim, query tokens, lengths, prefix): launches
+# small enough that their splits are finer than a batch's
+SMALL = {
+    # a shared prefix in chunks of 256 keys, a partial block past it
+    "decode-chunks": ("decode", 8, 2, 128, [1] * 3, [2100, 2049, 2563], 2048),
+    # one kv-head, 40 members: chunks limited by their workgroups
+    "decode-one-head": ("decode", 7, 1, 64, [1] * 40, [1600 + 9 * i for i in range(40)], 1584),
+    # no prefix: private ranges at the workspace bound's part count
+    "decode-private": ("decode", 32, 8, 128, [1, 1], [1000, 257], 0),
+    # 24-row row items beside the chunks
+    "verify-wide-rows": ("verify", 6, 2, 64, [8] * 3, [1040, 1999, 1033], 1024),
+}
+
+
+@pytest.mark.parametrize("name", list(SMALL))
+def test_small_launch_splits(name):
+    _gpu()
+    kind, hq, hkv, d, q_lens, lens, prefix = SMALL[name]
+    cfg = synth.AttnConfig(name, "bf16", hq, hkv, d, 16, 6200 + len(name))
+    errs, dev, _ = run_parity(launch_workload(cfg, q_lens, lens, 60, prefix), label=name)
+    say(name, "normalized errors", errs)
+    info = dev.infos[0]
+    assert info.n_groups > 0
+    if prefix:  # more than one chunk
+        row_tiles = -(-sum(q_lens) * (hq // hkv) // 128)
+        assert info.n_shared_items >= 2 * row_tiles * hkv

@@ -1,0 +1,66 @@
+"""Plans of small launches, whose key ranges are split finer than a batch's:
+every row produced exactly once, within the workspace bound, the decode
+array of the call without a workspace and the staging buffers' plan size."""
+import numpy as np
+import pytest
+
+from paper_2605_11232_amd import binding as B
+from paper_2605_11232_amd import synth
+from paper_2605_11232_amd.runtime import plan_words_bound
+from tests.test_capi_host import check_plan
+
+
+def _tables(r, L, prefix):
+    """Block tables of sequences that share their first prefix // 16 blocks."""
+    mb = int((L.max() + 15) // 16)
+    bt = np.full((len(L), mb), -1, np.int32)
+    nxt = 10 ** 6
+    for i, x in enumerate(L):
+        nb, p = int((x + 15) // 16), prefix // 16
+        bt[i, :p] = np.arange(p)
+        bt[i, p:nb] = np.arange(nxt, nxt + nb - p)
+        nxt += nb
+    return bt
+
+
+@pytest.mark.parametrize("kind", ["decode", "verify", "prefill", "mixed"])
+def test_small_launch_plans(kind):
+    r = np.random.default_rng(31)
+    code = {"decode": B.KIND_DECODE, "verify": B.KIND_VERIFY}.get(kind, B.KIND_PREFILL)
+    for trial in range(16):
+        n = int(r.integers(1, 6 if trial % 4 else 60))
+        hkv, G = int(r.choice([1, 2, 3, 4, 8])), int(r.choice([1, 4, 7, 8, 16]))
+        D = int(r.choice([64, 128]))
+        n_q = int(r.integers(2, 9))
+        prefix = int(r.choice([0, 256, 1000, 4096, 9000])) // 16 * 16
+        q = {"decode": np.ones(n), "verify": np.full(n, n_q),
+             "prefill": r.integers(1, 500, size=n),
+             "mixed": np.where(r.random(n) < 0.2, r.integers(1, 600, size=n), 1)}[kind].astype(int)
+        L = prefix + q + r.integers(0, int(r.choice([2, 700, 6000])), size=n)
+        cu = np.concatenate([[0], np.cumsum(q)])
+        bt = _tables(r, L, prefix)
+        for table in (bt, None):
+            plan, info = B.plan(code, n_q, L, cu, hkv * G, hkv, D, 16, B.PA_BF16, 256,
+                                block_table=table)
+            check_plan(plan, info, L, cu, G, hkv, D)
+            cfg = synth.AttnConfig("", "bf16", hkv * G, hkv, D, 16, 0)
+            assert info.plan_words <= plan_words_bound(cfg, n, int(cu[-1]), bt.shape[1])
+
+
+def test_decode_plans_keep_fitting_the_array_without_workspace():
+    """The finer splits never take a decode plan past the array that decode
+    without a workspace holds: 16 heads per kv-head, where the rows of one
+    part are the most, around the limit."""
+    fits = 0
+    for n in (8, 40, 60, 70, 100, 128):
+        for own in (40, 500, 1500, 5000):
+            L = np.full(n, 2048 + own + 1)
+            bt = _tables(None, L, 2048)
+            _, info = B.plan(B.KIND_DECODE, 1, L, np.arange(n + 1), 64, 4, 128, 16, B.PA_BF16,
+                             256, block_table=bt)
+            # a part per 256 private keys (at least one wavefront's share) and one shared
+            parts = 1 + -(-(own + 1) // 256)
+            if n * 64 * parts * 129 * 4 <= B.NOALLOC_WORKSPACE_BYTES:
+                assert info.workspace_bytes <= B.NOALLOC_WORKSPACE_BYTES
+                fits += 1
+    assert fits > 5
