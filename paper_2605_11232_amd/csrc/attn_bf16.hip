@@ -205,7 +205,7 @@ __device__ __forceinline__ void tile_item(const int32_t* it, int g, int poff, co
     hq = g * G + (rho - qi * G);
     part = it[I_PART] < 0 ? -1 : it[I_PART] + poff + lr;
     key_seq = r;
-    kend = min(it[I_KV1], L);
+    kend = min(it[I_KV1], L) - int(uint32_t(it[I_FLAGS]) / kItemPast);
     apos = valid ? L - n + qi : -1;
     // Rows are ordered by query, so the item's first row has the smallest
     // position: steps entirely at or below it need no causal mask.
@@ -848,8 +848,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_per_e
   }
 }
 
-// Combine split partial results by log-sum-exp: one workgroup per merge
-// group of at most four rows, half a wavefront per row (32 lanes over the
+// Combine split partial results by log-sum-exp: one workgroup per four rows (a
+// merge group, or a piece of a key-split tile's), half a wavefront per row (32 lanes over the
 // output dims, 16-byte partial loads).  The partial outputs of up to 16 parts
 // are requested before the part LSEs are reduced, so a row costs about one
 // memory round trip; parts are combined in split order (deterministic).
@@ -858,14 +858,18 @@ __global__ __launch_bounds__(kMergeRows * 32) void merge_kernel(AttnArgs a) {
   constexpr int VD = D / 32;  // output dims per lane
   constexpr int C = 16;       // parts whose loads are in flight together
   typedef float vecf __attribute__((ext_vector_type(VD)));
-  // merge group blockIdx.x: template blockIdx.x % N_GROUP_TMPL of kv-head
-  // blockIdx.x / N_GROUP_TMPL
-  const int ntg = a.plan[H_N_GROUP_TMPL];
-  const int g = blockIdx.x / ntg;
-  const int32_t* gr = a.plan + a.plan[H_GROUP_OFF] + (blockIdx.x - g * ntg) * kGroupWords;
-  const int lr = threadIdx.x >> 5, lane = threadIdx.x & 31;
+  const int narrow = a.plan[H_N_GROUP_NARROW];
+  const int g = blockIdx.y;
+  int t = blockIdx.x, sub = 0;  // template, and which of its rows
+  if (t >= narrow) {
+    sub = (t - narrow) % kWideGroupParts;
+    t = narrow + (t - narrow) / kWideGroupParts;
+  }
+  const int32_t* gr = a.plan + a.plan[H_GROUP_OFF] + t * kGroupWords;
+  const int lr = sub * kMergeRows + (threadIdx.x >> 5), lane = threadIdx.x & 31;
   const int half = threadIdx.x & 32;  // first lane of this row's half wavefront
   const int nrows = gr[G_NROWS];
+  if (sub * kMergeRows >= nrows) return;
   const bool valid = lr < nrows;
   const int r = gr[G_SEQ], row0 = gr[G_ROW0];
   const int nsplit = gr[G_NSPLIT], stride = gr[G_STRIDE];
@@ -986,10 +990,10 @@ int launch_attn_bf16(const void* q, const void* kc, const void* vc, int32_t num_
   if (n_groups > 0) {
     hipEvent_t start_here = grid > 0 ? nullptr : ev_start;
     if (d == 128)
-      hipExtLaunchKernelGGL(merge_kernel<128>, dim3(n_groups), dim3(kMergeRows * 32), 0, stream,
+      hipExtLaunchKernelGGL(merge_kernel<128>, dim3(n_groups / hkv, hkv), dim3(kMergeRows * 32), 0, stream,
                             start_here, ev_stop, 0, a);
     else
-      hipExtLaunchKernelGGL(merge_kernel<64>, dim3(n_groups), dim3(kMergeRows * 32), 0, stream,
+      hipExtLaunchKernelGGL(merge_kernel<64>, dim3(n_groups / hkv, hkv), dim3(kMergeRows * 32), 0, stream,
                             start_here, ev_stop, 0, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return static_cast<int>(e);

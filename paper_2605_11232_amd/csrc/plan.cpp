@@ -55,6 +55,7 @@ constexpr int64_t kMinRowKeys = 256;        // split target floor of row items
 // part count stays within the workspace bound: 4 decode requests on a
 // 2048-token prefix 19.4 us per append and call against 20.7 with 256 (128: even).
 constexpr int64_t kPlanRowKeys = 192;
+constexpr int64_t kSplitKeys = 512;         // fewest keys of a part of a key-split tile
 constexpr int64_t kTailWorkPct = 10;        // row work given half-length items (per cent)
 constexpr int64_t kStealPct = 5;            // tile work in the tail list (per cent)
 
@@ -153,6 +154,55 @@ void interleave(std::vector<U>& out, const std::vector<std::vector<U>>& queues) 
   }
 }
 
+// Keys per part of the launch's 128-row tile items (multiple of the tile
+// step), or 0 to leave them whole.  A launch of few tiles leaves most of the
+// chip idle while each walks its keys; splitting the keys gives more
+// workgroups, and costs the write and read of the parts and a merge launch.
+// The lengths tried are compared by an estimate of the call in microseconds,
+// fitted to the calls below: a step takes 1.25 with one workgroup per CU and 2.1
+// with two (1.3 at head_dim 64; whole tiles 1.2, beyond one per CU, where causal
+// lengths differ and end apart, 1.4), the merge 3 plus the parts at 4.5 TB/s, and
+// a split has to save 15 %.  More than two workgroups per CU are never made.
+// Append and call, 32/8 heads of 128: 389 new tokens of one request on 2048
+// cached ones (104 workgroups) 52.5 us whole, 39.7 in two parts, 35.9 in four;
+// 100 on 4096 (32) 83 and 26; head_dim 64, two requests of
+// 512 (256) 36.7 and 33.0.  Whole stays the better one for 1500 tokens with
+// nothing cached (376 workgroups, 41 us against 43.5) and two requests of
+// 300-700 on 2048 (250, 57.8 against 58.4).
+template <class IsRow>
+int64_t tile_split_keys(int32_t n_seqs, const int32_t* seq_lens, const int32_t* cu, int32_t G,
+                        int32_t hkv, int32_t head_dim, int32_t num_cus, IsRow is_row) {
+  std::vector<int64_t> kv;  // keys of each tile (of one kv-head)
+  int64_t rows = 0, longest = 0;
+  for (int32_t r = 0; r < n_seqs; ++r) {
+    const int64_t n = cu[r + 1] - cu[r];
+    if (n == 0 || is_row(r)) continue;
+    if (cdiv(n * G, pa::kTileRows) * hkv + int64_t(kv.size()) * hkv > 2 * num_cus) return 0;
+    for (int64_t row0 = 0; row0 < n * G; row0 += pa::kTileRows) {
+      const int64_t last = std::min(row0 + pa::kTileRows, n * G) - 1;
+      kv.push_back(seq_lens[r] - n + last / G + 1);
+      longest = std::max(longest, kv.back());
+    }
+    rows += n * G * hkv;
+  }
+  if (longest <= kSplitKeys) return 0;
+  auto steps = [](int64_t keys) { return double(cdiv(keys, pa::kTileStep)); };
+  double best = 0.85 * steps(longest) * (int64_t(kv.size()) * hkv <= num_cus ? 1.2 : 1.4);
+  int64_t best_keys = 0;
+  for (int64_t n = 2;; ++n) {
+    const int64_t keys = cdiv(cdiv(longest, n), pa::kTileStep) * pa::kTileStep;
+    if (keys < kSplitKeys) break;
+    int64_t parts = 0;
+    for (int64_t k : kv) parts += cdiv(k, keys);
+    if (parts * hkv > 2 * num_cus) break;
+    const double bytes = double(rows) * double(parts) / double(kv.size()) * 4 * (head_dim + 1);
+    const double step = parts * hkv <= num_cus ? 1.25 : head_dim == 64 ? 1.3 : 2.1;
+    const double t = steps(keys) * step + 3 + bytes / 4.5e6;
+    if (t < best) best = t, best_keys = keys;
+  }
+  return best_keys;
+}
+
 }  // namespace
 
 extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int32_t* seq_lens,
@@ -207,7 +257,7 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
   using Grp = std::array<int32_t, pa::kGroupWords>;
   using Ref = std::pair<int32_t, int32_t>;
   std::vector<Rec> t_shared, t_tiles, t_rows;
-  std::vector<Grp> t_groups;
+  std::vector<Grp> t_groups, t_wide;  // of at most kMergeRows rows; of a tile's rows
   std::vector<int32_t> t_members;  // head 0's member tables: (sequence, partial base) pairs
   std::vector<Rec> sorted_rows;    // row templates, longest first, padded to whole quads
   int64_t head_partial = 0;
@@ -369,6 +419,9 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
         split_rows(kMinRowKeys);
       }
     }
+    const int64_t split_keys =
+        tile_split_keys(n_seqs, seq_lens, cu_seqlens_q, G, num_kv_heads, head_dim, num_cus, is_row);
+
     std::vector<int64_t> tile_cost, row_cost, shared_cost;
     // head-0 partial base of a cascade member's merge group
     std::vector<int32_t> member_base(cg_keys.empty() ? 0 : size_t(n_seqs), -1);
@@ -435,8 +488,25 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
           const int32_t nrows = std::min(pa::kTileRows, rows - row0);
           const int32_t last_q = (row0 + nrows - 1) / G;
           const int32_t kv1 = L - n + last_q + 1;
-          t_tiles.push_back({r, 0, row0, nrows, 0, kv1, -1, 0});
-          tile_cost.push_back(int64_t(kv1) * nrows);
+          const int64_t nsplit = split_keys ? cdiv(kv1, split_keys) : 1;
+          if (nsplit == 1) {
+            t_tiles.push_back({r, 0, row0, nrows, 0, kv1, -1, 0});
+            tile_cost.push_back(int64_t(kv1) * nrows);
+            continue;
+          }
+          // equal key ranges covering [0, L), the last one marked with the keys
+          // past the tile's last row
+          const int32_t per = int32_t(cdiv(cdiv(kv1, nsplit), pa::kTileStep) * pa::kTileStep);
+          const int32_t used = int32_t(cdiv(kv1, per));
+          const int32_t base = int32_t(head_partial);
+          head_partial += int64_t(used) * nrows;
+          t_wide.push_back({r, 0, row0, nrows, used, base, nrows, 0});
+          for (int32_t sp = 0; sp < used; ++sp) {
+            const int32_t k0 = sp * per, k1 = std::min(kv1, k0 + per);
+            const int32_t past = sp + 1 == used ? L - kv1 : 0;
+            t_tiles.push_back({r, 0, row0, nrows, k0, k1 + past, base + sp * nrows, past * pa::kItemPast});
+            tile_cost.push_back(int64_t(k1 - k0) * nrows);
+          }
         }
       }
     }
@@ -570,7 +640,7 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
     // dispatch slots become wildcards that take tail items until none is
     // left anywhere: XCDs that run ahead take over the others' last items.
     static_assert(pa::kXcdQueues == kXcds, "one tail list per XCD queue");
-    if (kStealPct > 0) {
+    if (kStealPct > 0 && !split_keys) {
       const int32_t t_lo = int32_t(t_shared.size()), t_hi = t_lo + int32_t(t_tiles.size());
       auto stealable = [&](const Ref& r) {
         if (r.second < t_lo || r.second >= t_hi) return false;
@@ -596,7 +666,9 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
 
   const int64_t partial_rows = head_partial * num_kv_heads;
   const int64_t n_row = n_quads * 4;
-  const int64_t n_groups = int64_t(t_groups.size()) * num_kv_heads;
+  const int64_t n_narrow = int64_t(t_groups.size());
+  const int64_t n_groups = (n_narrow + int64_t(t_wide.size()) * pa::kWideGroupParts) * num_kv_heads;
+  t_groups.insert(t_groups.end(), t_wide.begin(), t_wide.end());
   const int64_t head_members = int64_t(t_members.size());
   const int64_t grid = dtype == PA_F32 ? int64_t(total_q) * num_q_heads
                                        : int64_t(dispatch.size());
@@ -654,7 +726,7 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
   h[pa::H_N_SHARED] = int32_t(n_shared_wg);
   h[pa::H_N_TILE] = int32_t(n_tile_wg);
   h[pa::H_N_ROW] = int32_t(n_row);
-  h[pa::H_N_GROUPS] = int32_t(n_groups);
+  h[pa::H_N_GROUPS] = int32_t(int64_t(t_groups.size()) * num_kv_heads);
   h[pa::H_GRID] = int32_t(grid);
   h[pa::H_HQ] = num_q_heads;
   h[pa::H_HKV] = num_kv_heads;
@@ -677,6 +749,7 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
   h[pa::H_N_TAIL] = int32_t(n_tail);
   h[pa::H_N_WILD] = int32_t(n_tail);  // one wildcard per tail item
   h[pa::H_CTR_OFF] = int32_t(ctr_off);
+  h[pa::H_N_GROUP_NARROW] = int32_t(n_narrow);
   if (dtype == PA_BF16) {
     int32_t* p = plan + dispatch_off;
     auto word = [](const Ref& r) { return (r.first << pa::kDispatchHeadShift) | r.second; };

@@ -17,9 +17,9 @@ constexpr int32_t kPlanMagic = 0x31304150;  // "PA01"
 // shared-prefix template i, the next N_TILE_TMPL indices the tile templates,
 // the rest the first of four row templates (one per wavefront); the kinds
 // may interleave in the dispatch list.  Kv-head g's items
-// write the partial rows of head 0's template plus g * HEAD_PARTIAL; merge
-// group b of the merge launch is group template b % N_GROUP_TMPL of kv-head
-// b / N_GROUP_TMPL.
+// write the partial rows of head 0's template plus g * HEAD_PARTIAL.  The
+// merge launch has, per kv-head, one workgroup for each of the first
+// N_GROUP_NARROW group templates and kWideGroupParts for each of the others.
 enum : int32_t {
   H_MAGIC = 0,
   H_KIND,
@@ -50,7 +50,8 @@ enum : int32_t {
   H_N_TAIL,        // tile items in all tail lists
   H_N_WILD,        // wildcard workgroups (dispatch words kWildcard), one per tail item
   H_CTR_OFF,       // word offset of the counters (kCounterWords apart; zero in a fresh plan)
-  H_PAD28, H_PAD29, H_PAD30, H_PAD31,
+  H_N_GROUP_NARROW, // merge-group templates of at most kMergeRows rows; the others hold a tile's
+  H_PAD29, H_PAD30, H_PAD31,
   kHeaderWords = 32
 };
 constexpr int32_t kDispatchHeadShift = 24;  // template index < 2^24 (all kinds), kv-head < 2^7
@@ -76,13 +77,16 @@ constexpr int32_t kCounterBlockWords = (kXcdQueues + 1) * kCounterWords;
 // final output; otherwise the item writes normalised partial outputs and
 // log-sum-exps at workspace rows part + (rho - row0).  seq = -1: empty slot.
 // flags: kItemStream = no other item reads the item's keys (a few-row
-// sequence's private key range), so its copies need not stay in L2.
+// sequence's private key range), so its copies need not stay in L2; flags /
+// kItemPast = keys at the end of the range that no row of the item sees (the
+// ranges of a key-split tile cover the whole sequence).
 enum : int32_t {
   I_SEQ = 0, I_KVH, I_ROW0, I_NROWS, I_KV0, I_KV1, I_PART, I_FLAGS,
   kItemWords = 8
 };
 
 constexpr int32_t kItemStream = 1;
+constexpr int32_t kItemPast = 2;
 
 // Shared-prefix item: gathered rows [row0, row0 + nrows) of a cascade group's
 // members (member m owns gathered rows m * rpm .. m * rpm + rpm - 1, its own
@@ -113,6 +117,7 @@ constexpr int32_t kVariantTail = 4;
 constexpr int32_t kTileRows = 128;    // rows per tile item (4 waves x 32)
 constexpr int32_t kRowItemRows = 32;  // rows per single-wave item (two 16-column MFMA tiles)
 constexpr int32_t kMergeRows = 4;     // rows per merge group (one wavefront each)
+constexpr int32_t kWideGroupParts = kTileRows / kMergeRows;  // merge workgroups of a wide group
 constexpr int32_t kRowSeqRows = 64;   // sequences with at most this many rows use row items
 constexpr int32_t kKeyStep = 32;      // keys per row-item inner iteration
 constexpr int32_t kRowItemBlocks = 64;  // most blocks (of 16 keys) one row item spans

@@ -63,7 +63,7 @@ def plan_words_bound(cfg, n_seqs: int, total_q: int, max_blocks_per_seq: int) ->
     """Upper bound on the plan size of a launch of n_seqs sequences and
     total_q query tokens (tile items, key-split items of at least 256 keys,
     merge groups, cascade member tables, per-XCD padding; in a small launch
-    the shared-prefix chunks that fill the chip)."""
+    the key-split tiles and shared-prefix chunks that fill the chip)."""
     max_keys = max_blocks_per_seq * cfg.block_size
     return 16384 + 32 + 8 * (cfg.num_kv_heads * (total_q * cfg.group // 128 + n_seqs)
                      + 2 * cfg.num_kv_heads * n_seqs * (max_keys // 256 + 2) + 64)

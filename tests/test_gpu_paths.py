@@ -128,3 +128,26 @@ def test_small_launch_splits(name):
     if prefix:  # more than one chunk
         row_tiles = -(-sum(q_lens) * (hq // hkv) // 128)
         assert info.n_shared_items >= 2 * row_tiles * hkv
+
+
+# (q heads, kv heads, head_dim, query tokens, lengths): tiles whose keys are
+# split: rows that a part's keys are all hidden from, a part of one step, a partial
+# last tile, a cached context that ends inside a step, head_dim 64
+TILE_SPLIT = [
+    (8, 2, 128, [100], [2100]),
+    (4, 4, 64, [129, 3], [1300, 700]),
+    (28, 4, 128, [65, 40], [577 + 64, 4000]),
+    (16, 1, 128, [600, 1], [1111, 900]),
+]
+
+
+@pytest.mark.parametrize("case", range(len(TILE_SPLIT)))
+def test_key_split_tiles(case):
+    _gpu()
+    hq, hkv, d, q_lens, lens = TILE_SPLIT[case]
+    cfg = synth.AttnConfig(f"split-{case}", "bf16", hq, hkv, d, 16, 6300 + case)
+    errs, dev, _ = run_parity(launch_workload(cfg, q_lens, lens, 80 + case), label=cfg.name)
+    say(f"{cfg.name} normalized errors", errs)
+    info = dev.infos[0]
+    tiles = sum(-(-q * (hq // hkv) // 128) for q in q_lens if q * (hq // hkv) > 64) * hkv
+    assert info.n_tile_items > tiles and info.n_merge_rows >= 128

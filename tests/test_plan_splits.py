@@ -7,7 +7,9 @@ import pytest
 from paper_2605_11232_amd import binding as B
 from paper_2605_11232_amd import synth
 from paper_2605_11232_amd.runtime import plan_words_bound
-from tests.test_capi_host import check_plan
+from tests.test_capi_host import H_N_GROUP_TMPL, check_plan
+
+H_N_GROUP_NARROW = 28  # header word: merge groups of at most four rows
 
 
 def _tables(r, L, prefix):
@@ -27,6 +29,7 @@ def _tables(r, L, prefix):
 def test_small_launch_plans(kind):
     r = np.random.default_rng(31)
     code = {"decode": B.KIND_DECODE, "verify": B.KIND_VERIFY}.get(kind, B.KIND_PREFILL)
+    split = 0
     for trial in range(16):
         n = int(r.integers(1, 6 if trial % 4 else 60))
         hkv, G = int(r.choice([1, 2, 3, 4, 8])), int(r.choice([1, 4, 7, 8, 16]))
@@ -45,6 +48,9 @@ def test_small_launch_plans(kind):
             check_plan(plan, info, L, cu, G, hkv, D)
             cfg = synth.AttnConfig("", "bf16", hkv * G, hkv, D, 16, 0)
             assert info.plan_words <= plan_words_bound(cfg, n, int(cu[-1]), bt.shape[1])
+            split += plan[H_N_GROUP_NARROW] < plan[H_N_GROUP_TMPL]
+    # some launches' tiles have split keys (merge groups of a tile's rows)
+    assert split > 0 or kind in ("decode", "verify")
 
 
 def test_decode_plans_keep_fitting_the_array_without_workspace():
