@@ -60,13 +60,15 @@ __device__ __forceinline__ float wave_xor(float v, int mask) { return __shfl_xor
 struct BlockWindow {
   const int32_t* row;
   int last;        // table index of the last block in use; later entries read it again
-  int num_blocks;  // ids are clamped to [0, num_blocks) when fetched
+  int num_blocks;  // ids are clamped to [0, num_blocks)
   int base;        // first block index held in `cur`
-  int cur, next;
+  int cur, next;   // next: as loaded, clamped when it becomes cur, so that nothing waits for it before
 
   __device__ __forceinline__ int fetch(int first) const {
     const int j = first + (threadIdx.x & 63);
-    const int id = row[j < last ? j : last];
+    return row[j < last ? j : last];
+  }
+  __device__ __forceinline__ int clamp(int id) const {
     return id < 0 ? 0 : (id >= num_blocks ? num_blocks - 1 : id);
   }
   __device__ __forceinline__ void init(const int32_t* r, int last_block, int nblocks, int first_block) {
@@ -74,7 +76,7 @@ struct BlockWindow {
     last = last_block;
     num_blocks = nblocks;
     base = first_block;
-    cur = fetch(base);
+    cur = clamp(fetch(base));
     next = fetch(base + 64);
   }
   // Make logical blocks jb .. jb + n - 1 readable with at() (wave-uniform;
@@ -84,7 +86,7 @@ struct BlockWindow {
   __device__ __forceinline__ void seek(int jb) {
     while (jb - base >= 64) {
       base += 64;
-      cur = next;
+      cur = clamp(next);
       next = fetch(base + 64);
     }
   }

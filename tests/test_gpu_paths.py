@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from paper_2605_11232_amd import synth
-from tests.parity import run_parity, say
+from tests.parity import LSE_TOL, TOL, close, run_parity, say
 
 pytestmark = pytest.mark.gpu
 
@@ -151,3 +151,40 @@ def test_key_split_tiles(case):
     info = dev.infos[0]
     tiles = sum(-(-q * (hq // hkv) // 128) for q in q_lens if q * (hq // hkv) > 64) * hkv
     assert info.n_tile_items > tiles and info.n_merge_rows >= 128
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_tile_rows_without_a_finite_first_score(d):
+    """The scores of a row's first keys (more than one 64-key step) are minus
+    infinity: the result is the softmax over the others, whose scores lie far
+    below zero; later keys raise the maximum by more than the tile path's
+    sums allow without moving its reference."""
+    _gpu()
+    from paper_2605_11232_amd.runtime import DeviceReplay
+    cfg = synth.AttnConfig(f"late-{d}", "bf16", 4, 2, d, 16, 6400 + d)
+    n, L, first = 130, 500, 100
+    wl = launch_workload(cfg, [n], [L], 91)
+    dev = DeviceReplay(wl).setup()
+    p = dev.prepare(wl.launches[0])
+    dev.append(p)
+    bt = p.block_table[0].long()
+    t = torch.arange(L, device="cuda")
+    off = t % 16
+    pos = (off & ~12) | ((off & 4) << 1) | ((off & 8) >> 1)
+    # dim 0 of the queries is 8 and that of a key sets its score
+    p.q[:, :, 0] = 8.0
+    k0 = torch.full((L,), -512.0, device="cuda")
+    k0[:first] = -float("inf")
+    k0[300:] = torch.linspace(-512.0, 64.0, L - 300, device="cuda")
+    dev.k_cache[bt[t // 16], :, 0, pos, 0] = k0.to(torch.bfloat16)[:, None]
+    dev.attend(p)
+    torch.cuda.synchronize()
+    k = dev.k_cache[bt[t // 16], :, :, pos].double().reshape(L, 2, d).permute(1, 2, 0).contiguous()
+    v = dev.v_cache[bt[t // 16], :, :, off].double().permute(1, 0, 2).contiguous()
+    q = p.q.double().view(n, 2, 2, d).permute(1, 0, 2, 3).reshape(2, 2 * n, d).contiguous()
+    s = torch.bmm(q, k).view(2, n, 2, L) * d ** -0.5
+    s.masked_fill_(t > (L - n + torch.arange(n, device="cuda"))[:, None, None], -float("inf"))
+    ref = torch.bmm(torch.softmax(s, 3).view(2, 2 * n, L), v).view(2, n, 2, d).permute(1, 0, 2, 3)
+    lse = torch.logsumexp(s, 3).permute(1, 0, 2).reshape(n, 4)
+    close(p.out.float().cpu().numpy(), ref.reshape(n, 4, d).cpu().numpy(), *TOL["bf16"], cfg.name)
+    close(p.lse.cpu().numpy(), lse.cpu().numpy(), *LSE_TOL["bf16"], cfg.name + " lse")
