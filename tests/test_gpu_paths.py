@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2605_11232_amd import synth
+from paper_2605_11232_amd import binding as B, synth
 from tests.parity import LSE_TOL, TOL, close, run_parity, say
 
 pytestmark = pytest.mark.gpu
@@ -188,3 +188,14 @@ def test_tile_rows_without_a_finite_first_score(d):
     lse = torch.logsumexp(s, 3).permute(1, 0, 2).reshape(n, 4)
     close(p.out.float().cpu().numpy(), ref.reshape(n, 4, d).cpu().numpy(), *TOL["bf16"], cfg.name)
     close(p.lse.cpu().numpy(), lse.cpu().numpy(), *LSE_TOL["bf16"], cfg.name + " lse")
+
+
+def test_calls_use_the_current_stream():
+    """A call without a stream argument goes to the stream torch has as current on the
+    current device, whichever it is, and an explicit one to itself."""
+    assert B._stream(None) == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert B._stream(None) == side.cuda_stream
+    assert B._stream(side) == B._stream(side.cuda_stream) == side.cuda_stream
+    assert B._stream(None) == torch.cuda.current_stream().cuda_stream
