@@ -49,13 +49,14 @@ namespace {
 constexpr int kXcds = 8;
 constexpr int64_t kRowWavesPerCu = 10;      // row-item split target
 constexpr int64_t kPrivateTileKeys = 4160;  // most private keys a few-row tile item covers
+constexpr int64_t kMinTileKeys = 256;       // fewest, in launches that leave compute units idle
 constexpr int64_t kMinRowKeys = 256;        // split target floor of row items
 // Fewest keys a row item is split down to in a launch without long sequences'
 // tiles (beside those the rows are not what it waits for), while the sequence's
 // part count stays within the workspace bound: 4 decode requests on a
 // 2048-token prefix 19.4 us per append and call against 20.7 with 256 (128: even).
 constexpr int64_t kPlanRowKeys = 192;
-constexpr int64_t kSplitKeys = 512;         // fewest keys of a part of a key-split tile
+constexpr int64_t kSplitKeys = 256;         // fewest keys of a part of a key-split tile
 constexpr int64_t kTailWorkPct = 10;        // row work given half-length items (per cent)
 constexpr int64_t kStealPct = 5;            // tile work in the tail list (per cent)
 
@@ -159,16 +160,19 @@ void interleave(std::vector<U>& out, const std::vector<std::vector<U>>& queues) 
 // chip idle while each walks its keys; splitting the keys gives more
 // workgroups, and costs the write and read of the parts and a merge launch.
 // The lengths tried are compared by an estimate of the call in microseconds,
-// fitted to the calls below: a step takes 1.25 with one workgroup per CU and 2.1
-// with two (1.3 at head_dim 64; whole tiles 1.2, beyond one per CU, where causal
-// lengths differ and end apart, 1.4), the merge 3 plus the parts at 4.5 TB/s, and
-// a split has to save 15 %.  More than two workgroups per CU are never made.
+// fitted to the calls below: a step takes 1.1 with at most a workgroup on every
+// other CU, 1.25 up to one per CU and 2.1 with two, 2 more for the call from one on
+// every other CU, as some get two; whole tiles 1.2, beyond one per CU, where causal
+// lengths differ and end apart, 1.4; at head_dim 64 about two thirds of that; the
+// merge takes 4 plus the parts at 4.5 TB/s; and a split has to save 15 %.  More than
+// two workgroups per CU are never made.
 // Append and call, 32/8 heads of 128: 389 new tokens of one request on 2048
 // cached ones (104 workgroups) 52.5 us whole, 39.7 in two parts, 35.9 in four;
-// 100 on 4096 (32) 83 and 26; head_dim 64, two requests of
+// 100 on 4096 (32) 83 and 26; 17-57 on 631 (16) 22 and 17; head_dim 64, two requests of
 // 512 (256) 36.7 and 33.0.  Whole stays the better one for 1500 tokens with
-// nothing cached (376 workgroups, 41 us against 43.5) and two requests of
-// 300-700 on 2048 (250, 57.8 against 58.4).
+// nothing cached (376 workgroups, 41 us against 43.5), two requests of
+// 300-700 on 2048 (250, 57.8 against 58.4), four of 42-154 on 195-700 (96,
+// 23 against 27 in parts of 256 keys), 540 tokens at head_dim 64 (136, 18 against 25).
 template <class IsRow>
 int64_t tile_split_keys(int32_t n_seqs, const int32_t* seq_lens, const int32_t* cu, int32_t G,
                         int32_t hkv, int32_t head_dim, int32_t num_cus, IsRow is_row) {
@@ -187,7 +191,8 @@ int64_t tile_split_keys(int32_t n_seqs, const int32_t* seq_lens, const int32_t* 
   }
   if (longest <= kSplitKeys) return 0;
   auto steps = [](int64_t keys) { return double(cdiv(keys, pa::kTileStep)); };
-  double best = 0.85 * steps(longest) * (int64_t(kv.size()) * hkv <= num_cus ? 1.2 : 1.4);
+  const double half_dim = head_dim == 64 ? 0.65 : 1;
+  double best = 0.85 * steps(longest) * (int64_t(kv.size()) * hkv <= num_cus ? 1.2 * half_dim : 1.4);
   int64_t best_keys = 0;
   for (int64_t n = 2;; ++n) {
     const int64_t keys = cdiv(cdiv(longest, n), pa::kTileStep) * pa::kTileStep;
@@ -196,8 +201,8 @@ int64_t tile_split_keys(int32_t n_seqs, const int32_t* seq_lens, const int32_t* 
     for (int64_t k : kv) parts += cdiv(k, keys);
     if (parts * hkv > 2 * num_cus) break;
     const double bytes = double(rows) * double(parts) / double(kv.size()) * 4 * (head_dim + 1);
-    const double step = parts * hkv <= num_cus ? 1.25 : head_dim == 64 ? 1.3 : 2.1;
-    const double t = steps(keys) * step + 3 + bytes / 4.5e6;
+    const double step = 2 * parts * hkv <= num_cus ? 1.1 : parts * hkv <= num_cus ? 1.25 : 2.1;
+    const double t = steps(keys) * step * half_dim + (2 * parts * hkv <= num_cus ? 4 : 6) + bytes / 4.5e6;
     if (t < best) best = t, best_keys = keys;
   }
   return best_keys;
@@ -326,13 +331,30 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
     // aim for enough single-wave items to keep kRowWavesPerCu wavefronts per
     // CU busy, a split target of at least kMinRowKeys and at most 1024 keys
     // per item (halved for the tail below).
-    int64_t row_keys = 0;
-    bool long_seqs = false;
+    int64_t row_keys = 0, long_tiles = 0;
+    std::vector<int64_t> few_tile_keys;  // private keys of the sequences on_tiles
     for (int32_t r = 0; r < n_seqs; ++r) {
-      if (is_row(r) && !on_tiles(r))
-        row_keys += int64_t(seq_lens[r] - kstart[r]) * num_kv_heads;
-      long_seqs = long_seqs || (qlen(r) > 0 && !is_row(r));
+      const int64_t keys = seq_lens[r] - kstart[r];
+      if (!is_row(r)) long_tiles += cdiv(int64_t(qlen(r)) * G, pa::kTileRows) * num_kv_heads;
+      else if (on_tiles(r)) few_tile_keys.push_back(keys);
+      else row_keys += keys * num_kv_heads;
     }
+    const bool long_seqs = long_tiles > 0;
+    // Private keys per tile item of a few-row sequence (33 to 64 rows).  An item
+    // walks its keys in series, so a launch that leaves compute units idle gets
+    // the shortest items that still come to one for each CU without a tile of a
+    // long sequence.  Append and call, us, of one item per sequence and of
+    // these: one verification of 6 tokens on 1800 keys, 64/8 heads, 33 and 14; 5 on
+    // 3000-3500 past a prefix, 28/4 heads, 63 and 23; 8 on 6000-9000 83 and 52;
+    // 32 on 4100 fill the chip and stay whole.
+    int64_t tile_keys = kPrivateTileKeys;
+    auto tile_items = [&](int64_t keys) {
+      int64_t n = 0;
+      for (int64_t k : few_tile_keys) n += cdiv(k, keys) * num_kv_heads;
+      return n;
+    };
+    if (tile_items(kPrivateTileKeys) < num_cus - long_tiles)
+      for (tile_keys = kMinTileKeys; tile_items(tile_keys) > num_cus - long_tiles;) tile_keys += pa::kTileStep;
     const int64_t target_waves = int64_t(num_cus) * kRowWavesPerCu;
     // The sequences with the fewest private keys, up to kTailWork of the row
     // work, get half-length items: ordered longest first, those run last, so
@@ -363,7 +385,9 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
       const int64_t L = seq_lens[r], len = L - kstart[r];
       const int64_t most = cdiv(L, kMinRowKeys) + (L > pa::kSharedMinKeys ? cdiv(L, pa::kSharedChunk) : 0) -
                            (cgroup[r] >= 0 ? cg_chunks[cgroup[r]] : 0);
-      return std::max<int64_t>(1, std::min(cdiv(len, on_tiles(r) ? kPrivateTileKeys : row_chunk[r]), most));
+      // an item of up to 512 keys that needs no merge is not split into two that do
+      if (on_tiles(r) && cgroup[r] < 0 && len <= 2 * kMinTileKeys) return int64_t{1};
+      return std::max<int64_t>(1, std::min(cdiv(len, on_tiles(r) ? tile_keys : row_chunk[r]), most));
     };
     for (int32_t S : cg_keys) cg_chunks.push_back(int32_t(cdiv(S, pa::kSharedChunk)));
     split_rows(long_seqs ? kMinRowKeys : kPlanRowKeys);
@@ -432,7 +456,7 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
         if (qlen(r) == 0) continue;
         if (is_row(r)) ng += cdiv(qlen(r) * G, pa::kMergeRows);
         if (is_row(r) && on_tiles(r))
-          nt += cdiv(seq_lens[r] - kstart[r], kPrivateTileKeys);
+          nt += private_parts(r);
         else if (is_row(r))
           nr += private_parts(r);
         else
@@ -640,7 +664,8 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
     // dispatch slots become wildcards that take tail items until none is
     // left anywhere: XCDs that run ahead take over the others' last items.
     static_assert(pa::kXcdQueues == kXcds, "one tail list per XCD queue");
-    if (kStealPct > 0 && !split_keys) {
+    // A launch whose workgroups all start at once has no last ones to take.
+    if (kStealPct > 0 && !split_keys && int64_t(dispatch.size()) > 2 * num_cus) {
       const int32_t t_lo = int32_t(t_shared.size()), t_hi = t_lo + int32_t(t_tiles.size());
       auto stealable = [&](const Ref& r) {
         if (r.second < t_lo || r.second >= t_hi) return false;

@@ -113,6 +113,9 @@ SMALL = {
     "decode-private": ("decode", 32, 8, 128, [1, 1], [1000, 257], 0),
     # 24-row row items beside the chunks
     "verify-wide-rows": ("verify", 6, 2, 64, [8] * 3, [1040, 1999, 1033], 1024),
+    # 40 rows: private tile items split to a few steps each, alone and past a prefix
+    "verify-tiles": ("verify", 16, 2, 128, [5] * 3, [1000, 515, 2053], 0),
+    "verify-tiles-prefix": ("verify", 16, 2, 64, [5] * 3, [2000, 1030, 1800], 1024),
 }
 
 

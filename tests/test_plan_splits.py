@@ -70,3 +70,29 @@ def test_decode_plans_keep_fitting_the_array_without_workspace():
                 assert info.workspace_bytes <= B.NOALLOC_WORKSPACE_BYTES
                 fits += 1
     assert fits > 5
+
+
+def test_few_row_tiles_fill_idle_compute_units():
+    """33 to 64 rows per sequence: a launch that leaves compute units idle gets more
+    items, one per compute unit at most; one key range of up to 512 keys that needs
+    no merge stays whole, and so does everything once the sequences fill the chip."""
+    for n, own, hkv, prefix, more in [(1, 512, 8, 0, False), (1, 513, 8, 0, True), (1, 9000, 8, 0, True),
+                                      (5, 3000, 4, 768, True), (16, 700, 8, 0, True), (31, 700, 8, 0, True),
+                                      (32, 4100, 8, 4096, False), (33, 4100, 8, 0, False)]:
+        L = np.full(n, prefix + own)
+        L[1:] -= own // 3
+        cu = np.arange(n + 1) * 5
+        plan, info = B.plan(B.KIND_VERIFY, 5, L, cu, 8 * hkv, hkv, 128, 16, B.PA_BF16, 256,
+                            block_table=_tables(None, L, prefix))
+        check_plan(plan, info, L, cu, 8, hkv, 128)
+        whole = n * hkv
+        assert whole <= info.n_tile_items <= max(whole, 256)
+        assert (info.n_tile_items > whole) == more
+
+
+def test_launches_that_start_at_once_have_no_tail_lists():
+    for n, tail in [(1, False), (16, False), (17, True)]:  # 32 full tiles each: 512 start at once
+        L = np.full(n, 256)
+        plan, info = B.plan(B.KIND_PREFILL, 0, L, np.arange(n + 1) * 128, 32, 8, 128, 16, B.PA_BF16, 256)
+        check_plan(plan, info, L, np.arange(n + 1) * 128, 4, 8, 128)
+        assert bool(info.variant & 4) == tail
