@@ -346,14 +346,19 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
     // long sequence.  Append and call, us, of one item per sequence and of
     // these: one verification of 6 tokens on 1800 keys, 64/8 heads, 33 and 14; 5 on
     // 3000-3500 past a prefix, 28/4 heads, 63 and 23; 8 on 6000-9000 83 and 52;
-    // 32 on 4100 fill the chip and stay whole.
+    // 32 on 4100 fill the chip and stay whole.  So do items beside a shared prefix of
+    // several coarse chunks, where the chunk and item counts are fixed by the plan's
+    // contract (4 verifications of 5 tokens on 16384 shared and 4096 private keys: 3
+    // chunks, one private item each, 101 us; splitting both would take 41).
+    int64_t longest_prefix = 0;
+    for (int32_t S : cg_keys) longest_prefix = std::max<int64_t>(longest_prefix, S);
     int64_t tile_keys = kPrivateTileKeys;
     auto tile_items = [&](int64_t keys) {
       int64_t n = 0;
       for (int64_t k : few_tile_keys) n += cdiv(k, keys) * num_kv_heads;
       return n;
     };
-    if (tile_items(kPrivateTileKeys) < num_cus - long_tiles)
+    if (longest_prefix <= pa::kSharedChunk && tile_items(kPrivateTileKeys) < num_cus - long_tiles)
       for (tile_keys = kMinTileKeys; tile_items(tile_keys) > num_cus - long_tiles;) tile_keys += pa::kTileStep;
     const int64_t target_waves = int64_t(num_cus) * kRowWavesPerCu;
     // The sequences with the fewest private keys, up to kTailWork of the row
@@ -664,8 +669,13 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
     // dispatch slots become wildcards that take tail items until none is
     // left anywhere: XCDs that run ahead take over the others' last items.
     static_assert(pa::kXcdQueues == kXcds, "one tail list per XCD queue");
-    // A launch whose workgroups all start at once has no last ones to take.
-    if (kStealPct > 0 && !split_keys && int64_t(dispatch.size()) > 2 * num_cus) {
+    // A launch of few workgroups, which all start at once, has no last ones to
+    // take: the lists only cost it round trips to the counters (116 tiles of 12-34
+    // tokens 14.1 us per append and call with them, 11.4 without; 64 tiles 13.5 and
+    // 11.0).  Up to two workgroups per CU start at once and would gain the same 2 us;
+    // the line is at one on every other CU because plans above it (192 workgroups)
+    // are relied on to have lists.
+    if (kStealPct > 0 && !split_keys && 2 * int64_t(dispatch.size()) > num_cus) {
       const int32_t t_lo = int32_t(t_shared.size()), t_hi = t_lo + int32_t(t_tiles.size());
       auto stealable = [&](const Ref& r) {
         if (r.second < t_lo || r.second >= t_hi) return false;

@@ -90,8 +90,8 @@ def test_few_row_tiles_fill_idle_compute_units():
         assert (info.n_tile_items > whole) == more
 
 
-def test_launches_that_start_at_once_have_no_tail_lists():
-    for n, tail in [(1, False), (16, False), (17, True)]:  # 32 full tiles each: 512 start at once
+def test_launches_of_few_workgroups_have_no_tail_lists():
+    for n, tail in [(1, False), (4, False), (5, True)]:  # 32 full tiles each
         L = np.full(n, 256)
         plan, info = B.plan(B.KIND_PREFILL, 0, L, np.arange(n + 1) * 128, 32, 8, 128, 16, B.PA_BF16, 256)
         check_plan(plan, info, L, np.arange(n + 1) * 128, 4, 8, 128)
