@@ -540,7 +540,7 @@ __device__ __forceinline__ void tile_item(const int32_t* it, int g, int poff, co
         for (int e = 0; e < 4; ++e) o4[e] = acc[dt][4 * q4 + e] * inv;
         *reinterpret_cast<f32x4*>(op + d) = o4;
       }
-    if (hh == 0) a.ws_lse[part] = lse_v;
+    if (hh == 0) a.ws_lse[part] = l == l ? lse_v : l;
   }
 }
 
@@ -731,7 +731,7 @@ __device__ __forceinline__ void row_item(const int32_t* it, int g, int poff, con
       float* op = a.ws_o + (int64_t)prow * D + 4 * g4;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4*>(op + 16 * dt) = acc[c][dt] * inv;
-      if (g4 == 0) a.ws_lse[prow] = lse_v;
+      if (g4 == 0) a.ws_lse[prow] = l[c] == l[c] ? lse_v : l[c];
     }
   }
 }
@@ -867,7 +867,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_per_e
 // merge group, or a piece of a key-split tile's), half a wavefront per row (32 lanes over the
 // output dims, 16-byte partial loads).  The partial outputs of up to 16 parts
 // are requested before the part LSEs are reduced, so a row costs about one
-// memory round trip; parts are combined in split order (deterministic).
+// memory round trip; parts are combined in split order (deterministic).  A part
+// whose sum is NaN has the log-sum-exp NaN, so that the row comes out NaN.
 template <int D>
 __global__ __launch_bounds__(kMergeRows * 32) void merge_kernel(AttnArgs a) {
   constexpr int VD = D / 32;  // output dims per lane
@@ -910,7 +911,16 @@ __global__ __launch_bounds__(kMergeRows * 32) void merge_kernel(AttnArgs a) {
   for (int o = 16; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
   vecf o_acc = {};
   float lse_v = kNegInf;
-  if (mx != kNegInf) {
+  if (mx == kNegInf) {
+    // no part has a sum above zero: zeros, or NaN where the parts hold it (a
+    // row without a finite score must not come out as zeros)
+    for (int s0 = 0; s0 < nsplit; s0 += C) {
+      if (s0 > 0) load_batch(s0);
+#pragma unroll
+      for (int u = 0; u < C; ++u)
+        if (s0 + u < nsplit) o_acc += 0.f * x[u];
+    }
+  } else {
     float sum = lse0 == kNegInf ? 0.f : exp2f((lse0 - mx) * kLog2e);
     for (int s = 32 + lane; s - lane < nsplit; s += 32)
       if (s < nsplit) sum += exp2f((part_lse(s) - mx) * kLog2e);
@@ -943,7 +953,8 @@ __global__ __launch_bounds__(kMergeRows * 32) void merge_kernel(AttnArgs a) {
   __bf16* op = a.out + ((int64_t)(qs + qi) * a.hq + hq) * D + VD * lane;
   if constexpr (VD == 4) *reinterpret_cast<u32x2*>(op) = __builtin_bit_cast(u32x2, ob);
   else *reinterpret_cast<uint32_t*>(op) = __builtin_bit_cast(uint32_t, ob);
-  if (a.lse && lane == 0) a.lse[(int64_t)(qs + qi) * a.hq + hq] = lse_v;
+  // a NaN sum: minus infinity, as where one item writes the row
+  if (a.lse && lane == 0) a.lse[(int64_t)(qs + qi) * a.hq + hq] = lse_v == lse_v ? lse_v : kNegInf;
 }
 
 }  // namespace

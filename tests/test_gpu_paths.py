@@ -202,3 +202,48 @@ def test_calls_use_the_current_stream():
         assert B._stream(None) == side.cuda_stream
     assert B._stream(side) == B._stream(side.cuda_stream) == side.cuda_stream
     assert B._stream(None) == torch.cuda.current_stream().cuda_stream
+
+
+# (kind, q heads, kv heads, head_dim, query tokens, lengths, prefix): rows merged
+# from key-split tiles, few-row tiles, row items, a shared prefix's chunks, and
+# whole tiles beside them
+NAN = {
+    "tiles": ("prefill", 8, 2, 128, [100], [2100], 0),
+    "tiles-whole": ("prefill", 8, 2, 128, [100], [120], 0),
+    "verify-tiles": ("verify", 16, 2, 64, [5] * 2, [1000, 2053], 0),
+    "decode": ("decode", 32, 8, 128, [1, 1], [1000, 257], 0),
+    "decode-shared": ("decode", 8, 2, 128, [1] * 3, [2100, 2049, 2563], 2048),
+}
+
+
+@pytest.mark.parametrize("where", ["query", "key"])
+@pytest.mark.parametrize("name", list(NAN))
+def test_rows_without_a_number_stay_visible(name, where):
+    """A row whose query, or a key it sees, is NaN comes out NaN (its log-sum-exp
+    minus infinity) however its keys are split; no other row is touched."""
+    _gpu()
+    from paper_2605_11232_amd.runtime import DeviceReplay
+    kind, hq, hkv, d, q_lens, lens, prefix = NAN[name]
+    cfg = synth.AttnConfig(f"nan-{name}", "bf16", hq, hkv, d, 16, 6500 + len(name))
+    dev = DeviceReplay(launch_workload(cfg, q_lens, lens, 61, prefix)).setup()
+    p = dev.prepare(dev.wl.launches[0])
+    dev.append(p)
+    dev.attend(p)
+    plain = p.out.float().cpu().numpy()
+    bad = torch.zeros(plain.shape[:2], dtype=torch.bool)
+    if where == "query":
+        p.q[q_lens[0] - 1, 1, 3] = float("nan")
+        bad[q_lens[0] - 1, 1] = True
+    else:
+        # the last token's key, of the first kv-head, in the first sequence: its last query
+        slot = int(p.slots[q_lens[0] - 1])
+        off = slot % 16
+        pos = (off & ~12) | ((off & 4) << 1) | ((off & 8) >> 1)
+        dev.k_cache[slot // 16, 0, 0, pos, 3] = float("nan")
+        bad[q_lens[0] - 1, :hq // hkv] = True
+    dev.attend(p)
+    torch.cuda.synchronize()
+    out, lse = p.out.float().cpu(), p.lse.cpu()
+    assert torch.equal(torch.isnan(out).all(2), bad) and torch.equal(torch.isnan(out).any(2), bad)
+    assert torch.equal(lse == -float("inf"), bad)
+    close(out[~bad].numpy(), plain[~bad.numpy()], *TOL["bf16"], cfg.name)
