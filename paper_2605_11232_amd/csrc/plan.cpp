@@ -165,7 +165,7 @@ void interleave(std::vector<U>& out, const std::vector<std::vector<U>>& queues) 
 // every other CU, as some get two; whole tiles 1.2, beyond one per CU, where causal
 // lengths differ and end apart, 1.4; at head_dim 64 about two thirds of that; the
 // merge takes 4 plus the parts at 4.5 TB/s; and a split has to save 15 %.  More than
-// two workgroups per CU are never made.
+// two workgroups per CU are never made, nor parts of more than most_bytes.
 // Append and call, 32/8 heads of 128: 389 new tokens of one request on 2048
 // cached ones (104 workgroups) 52.5 us whole, 39.7 in two parts, 35.9 in four;
 // 100 on 4096 (32) 83 and 26; 17-57 on 631 (16) 22 and 17; head_dim 64, two requests of
@@ -175,8 +175,9 @@ void interleave(std::vector<U>& out, const std::vector<std::vector<U>>& queues) 
 // 23 against 27 in parts of 256 keys), 540 tokens at head_dim 64 (136, 18 against 25).
 template <class IsRow>
 int64_t tile_split_keys(int32_t n_seqs, const int32_t* seq_lens, const int32_t* cu, int32_t G,
-                        int32_t hkv, int32_t head_dim, int32_t num_cus, IsRow is_row) {
-  std::vector<int64_t> kv;  // keys of each tile (of one kv-head)
+                        int32_t hkv, int32_t head_dim, int32_t num_cus, int64_t most_bytes,
+                        IsRow is_row) {
+  std::vector<int64_t> kv, tile_rows;  // keys and rows of each tile (of one kv-head)
   int64_t rows = 0, longest = 0;
   for (int32_t r = 0; r < n_seqs; ++r) {
     const int64_t n = cu[r + 1] - cu[r];
@@ -185,6 +186,7 @@ int64_t tile_split_keys(int32_t n_seqs, const int32_t* seq_lens, const int32_t* 
     for (int64_t row0 = 0; row0 < n * G; row0 += pa::kTileRows) {
       const int64_t last = std::min(row0 + pa::kTileRows, n * G) - 1;
       kv.push_back(seq_lens[r] - n + last / G + 1);
+      tile_rows.push_back(last - row0 + 1);
       longest = std::max(longest, kv.back());
     }
     rows += n * G * hkv;
@@ -197,9 +199,13 @@ int64_t tile_split_keys(int32_t n_seqs, const int32_t* seq_lens, const int32_t* 
   for (int64_t n = 2;; ++n) {
     const int64_t keys = cdiv(cdiv(longest, n), pa::kTileStep) * pa::kTileStep;
     if (keys < kSplitKeys) break;
-    int64_t parts = 0;
-    for (int64_t k : kv) parts += cdiv(k, keys);
-    if (parts * hkv > 2 * num_cus) break;
+    int64_t parts = 0, partial_rows = 0;
+    for (size_t i = 0; i < kv.size(); ++i) {
+      const int64_t p = cdiv(kv[i], keys);
+      parts += p;
+      if (p > 1) partial_rows += p * tile_rows[i];
+    }
+    if (parts * hkv > 2 * num_cus || partial_rows * hkv * (head_dim + 1) * 4 > most_bytes) break;
     const double bytes = double(rows) * double(parts) / double(kv.size()) * 4 * (head_dim + 1);
     const double step = 2 * parts * hkv <= num_cus ? 1.1 : parts * hkv <= num_cus ? 1.25 : 2.1;
     const double t = steps(keys) * step * half_dim + (2 * parts * hkv <= num_cus ? 4 : 6) + bytes / 4.5e6;
@@ -448,8 +454,11 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
         split_rows(kMinRowKeys);
       }
     }
-    const int64_t split_keys =
-        tile_split_keys(n_seqs, seq_lens, cu_seqlens_q, G, num_kv_heads, head_dim, num_cus, is_row);
+    // Decode of more than 64 heads per kv-head runs on these tiles, and whole
+    // they need no workspace: such a plan fits the same array.
+    const int64_t split_keys = tile_split_keys(
+        n_seqs, seq_lens, cu_seqlens_q, G, num_kv_heads, head_dim, num_cus,
+        kind == PA_KIND_DECODE ? int64_t(PA_NOALLOC_WORKSPACE_BYTES) : INT64_MAX, is_row);
 
     std::vector<int64_t> tile_cost, row_cost, shared_cost;
     // head-0 partial base of a cascade member's merge group

@@ -72,6 +72,24 @@ def test_decode_plans_keep_fitting_the_array_without_workspace():
     assert fits > 5
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_decode_plans_of_many_heads_fit_the_array_without_workspace(D):
+    """More than 64 heads per kv-head: such decode runs on tile items, which need no
+    workspace whole, so their key splits never take a plan past the array."""
+    split = 0
+    for hkv, G in [(1, 96), (1, 128), (2, 128), (1, 256), (2, 256)]:
+        for n in (1, 4, 8, 16, 64):
+            for own in (700, 8192, 65536, 131072):
+                L = np.full(n, own)
+                L[1:] -= 3
+                plan, info = B.plan(B.KIND_DECODE, 1, L, np.arange(n + 1), hkv * G, hkv, D, 16, B.PA_BF16, 256)
+                assert info.workspace_bytes <= B.NOALLOC_WORKSPACE_BYTES
+                split += info.workspace_bytes > 0
+                if own < 10000:
+                    check_plan(plan, info, L, np.arange(n + 1), G, hkv, D)
+    assert split > 20
+
+
 def test_few_row_tiles_fill_idle_compute_units():
     """33 to 64 rows per sequence: a launch that leaves compute units idle gets more
     items, one per compute unit at most; one key range of up to 512 keys that needs
