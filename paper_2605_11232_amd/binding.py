@@ -56,7 +56,7 @@ class PlanInfo(C.Structure):
     _fields_ = [("kind", C.c_int32), ("n_q", C.c_int32), ("n_shared_items", C.c_int32),
                 ("n_tile_items", C.c_int32), ("n_row_items", C.c_int32), ("n_groups", C.c_int32),
                 ("n_merge_rows", C.c_int32), ("grid", C.c_int32), ("variant", C.c_int32),
-                ("reserved", C.c_int32), ("plan_words", C.c_int64), ("workspace_bytes", C.c_int64),
+                ("n_merge_items", C.c_int32), ("plan_words", C.c_int64), ("workspace_bytes", C.c_int64),
                 ("n_seqs", C.c_int32), ("total_q", C.c_int32), ("num_q_heads", C.c_int32),
                 ("num_kv_heads", C.c_int32), ("head_dim", C.c_int32), ("dtype", C.c_int32),
                 ("partial_rows", C.c_int64)]

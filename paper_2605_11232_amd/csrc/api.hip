@@ -12,7 +12,7 @@ namespace dev {
 int launch_attn_bf16(const void* q, const void* kc, const void* vc, int32_t num_blocks,
                      const int32_t* bt, int32_t max_blocks, const int32_t* seq_lens,
                      const int32_t* cu_q, int32_t hq, int32_t hkv, int32_t d, float scale,
-                     const int32_t* plan, int32_t grid, int32_t n_tile, int32_t n_groups,
+                     const int32_t* plan, int32_t grid, int32_t n_tile, int32_t n_merge,
                      bool wide_rows, bool tail, int64_t partial_rows, void* ws, void* out,
                      float* lse, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
 int launch_attn_f32(const void* q, const void* kc, const void* vc, int32_t num_blocks,
@@ -130,8 +130,10 @@ int attn_common(const char* fn, int32_t want_kind, const void* q, const void* k_
                               head_dim, scale, out, lse, st, ev_start, ev_stop);
   } else {
     if (!plan) return fail(PA_ERR_ARG, "%s: NULL plan", fn);
-    if ((info->variant & ~(kVariantWideRows | kVariantTail)) != kVariantBf16 || info->grid < 0 ||
-        info->n_groups < 0 ||
+    const int32_t n_merge =
+        info->variant & kVariantWideGroups ? info->n_merge_items : info->n_groups;
+    if ((info->variant & ~(kVariantWideRows | kVariantTail | kVariantWideGroups)) != kVariantBf16 ||
+        info->grid < 0 || info->n_groups < 0 || n_merge < info->n_groups ||
         info->n_tile_items < 0 || info->n_shared_items < 0 ||
         int64_t(info->n_tile_items) + info->n_shared_items > info->grid ||
         info->partial_rows < 0 ||
@@ -160,7 +162,7 @@ int attn_common(const char* fn, int32_t want_kind, const void* q, const void* k_
     rc = dev::launch_attn_bf16(q, k_cache, v_cache, num_blocks, block_table, max_blocks_per_seq,
                                seq_lens, cu_seqlens_q, num_q_heads, num_kv_heads, head_dim, scale,
                                plan, info->grid, info->n_shared_items + info->n_tile_items,
-                               info->n_groups, (info->variant & kVariantWideRows) != 0,
+                               n_merge, (info->variant & kVariantWideRows) != 0,
                                (info->variant & kVariantTail) != 0,
                                partial_rows,
                                workspace, out, lse, st, ev_start, ev_stop);

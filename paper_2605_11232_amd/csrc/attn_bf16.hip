@@ -874,7 +874,8 @@ __global__ __launch_bounds__(kMergeRows * 32) void merge_kernel(AttnArgs a) {
   constexpr int VD = D / 32;  // output dims per lane
   constexpr int C = 16;       // parts whose loads are in flight together
   typedef float vecf __attribute__((ext_vector_type(VD)));
-  const int narrow = a.plan[H_N_GROUP_NARROW];
+  const int n_tmpl = a.plan[H_N_GROUP_TMPL];
+  const int narrow = int(gridDim.x) == n_tmpl ? n_tmpl : a.plan[H_N_GROUP_NARROW];
   const int g = blockIdx.y;
   int t = blockIdx.x, sub = 0;  // template, and which of its rows
   if (t >= narrow) {
@@ -962,7 +963,7 @@ __global__ __launch_bounds__(kMergeRows * 32) void merge_kernel(AttnArgs a) {
 int launch_attn_bf16(const void* q, const void* kc, const void* vc, int32_t num_blocks,
                      const int32_t* bt, int32_t max_blocks, const int32_t* seq_lens,
                      const int32_t* cu_q, int32_t hq, int32_t hkv, int32_t d, float scale,
-                     const int32_t* plan, int32_t grid, int32_t n_tile, int32_t n_groups,
+                     const int32_t* plan, int32_t grid, int32_t n_tile, int32_t n_merge,
                      bool wide_rows, bool tail, int64_t partial_rows, void* ws, void* out,
                      float* lse, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
   AttnArgs a;
@@ -990,7 +991,7 @@ int launch_attn_bf16(const void* q, const void* kc, const void* vc, int32_t num_
     const int mix = (n_tile == 0 ? (wide_rows ? 6 : 2) : (rows ? 7 : 1)) | (tail ? 8 : 0);
     // the caller's timing events ride on the dispatches (start on the first
     // kernel, stop on the last): no event packets between the kernels
-    hipEvent_t stop_here = n_groups > 0 ? nullptr : ev_stop;
+    hipEvent_t stop_here = n_merge > 0 ? nullptr : ev_stop;
 #define PA_LAUNCH(DD, MM)                                                                     \
   hipExtLaunchKernelGGL((attn_bf16_kernel<DD, MM>), dim3(grid), dim3(256), 0, stream, ev_start, \
                         stop_here, 0, a)
@@ -1013,18 +1014,18 @@ int launch_attn_bf16(const void* q, const void* kc, const void* vc, int32_t num_
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return static_cast<int>(e);
   }
-  if (n_groups > 0) {
+  if (n_merge > 0) {
     hipEvent_t start_here = grid > 0 ? nullptr : ev_start;
     if (d == 128)
-      hipExtLaunchKernelGGL(merge_kernel<128>, dim3(n_groups / hkv, hkv), dim3(kMergeRows * 32), 0, stream,
+      hipExtLaunchKernelGGL(merge_kernel<128>, dim3(n_merge / hkv, hkv), dim3(kMergeRows * 32), 0, stream,
                             start_here, ev_stop, 0, a);
     else
-      hipExtLaunchKernelGGL(merge_kernel<64>, dim3(n_groups / hkv, hkv), dim3(kMergeRows * 32), 0, stream,
+      hipExtLaunchKernelGGL(merge_kernel<64>, dim3(n_merge / hkv, hkv), dim3(kMergeRows * 32), 0, stream,
                             start_here, ev_stop, 0, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return static_cast<int>(e);
   }
-  if (grid <= 0 && n_groups <= 0) {
+  if (grid <= 0 && n_merge <= 0) {
     // nothing launched: the events still mark this point of the stream
     for (hipEvent_t ev : {ev_start, ev_stop}) {
       const hipError_t e = ev ? hipEventRecord(ev, stream) : hipSuccess;

@@ -711,7 +711,7 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
   const int64_t partial_rows = head_partial * num_kv_heads;
   const int64_t n_row = n_quads * 4;
   const int64_t n_narrow = int64_t(t_groups.size());
-  const int64_t n_groups = (n_narrow + int64_t(t_wide.size()) * pa::kWideGroupParts) * num_kv_heads;
+  const int64_t n_merge = (n_narrow + int64_t(t_wide.size()) * pa::kWideGroupParts) * num_kv_heads;
   t_groups.insert(t_groups.end(), t_wide.begin(), t_wide.end());
   const int64_t head_members = int64_t(t_members.size());
   const int64_t grid = dtype == PA_F32 ? int64_t(total_q) * num_q_heads
@@ -741,7 +741,8 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
   info->n_shared_items = int32_t(n_shared_wg);
   info->n_tile_items = int32_t(n_tile_wg);
   info->n_row_items = int32_t(n_row);
-  info->n_groups = int32_t(n_groups);
+  info->n_groups = int32_t(int64_t(t_groups.size()) * num_kv_heads);
+  info->n_merge_items = int32_t(n_merge);
   info->n_merge_rows = 0;
   for (const auto& g : t_groups) info->n_merge_rows += int64_t(g[pa::G_NROWS]) * num_kv_heads;
   info->grid = int32_t(grid);
@@ -749,7 +750,8 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
   for (const auto& it : t_rows) wide = wide || it[pa::I_NROWS] > 16;
   info->variant = dtype == PA_F32 ? 0
                                   : (pa::kVariantBf16 | (wide ? pa::kVariantWideRows : 0) |
-                                     (n_tail ? pa::kVariantTail : 0));
+                                     (n_tail ? pa::kVariantTail : 0) |
+                                     (t_wide.empty() ? 0 : pa::kVariantWideGroups));
   info->plan_words = words;
   info->workspace_bytes = partial_rows * int64_t(head_dim + 1) * int64_t(sizeof(float));
   info->n_seqs = n_seqs;

@@ -247,3 +247,25 @@ def test_rows_without_a_number_stay_visible(name, where):
     assert torch.equal(torch.isnan(out).all(2), bad) and torch.equal(torch.isnan(out).any(2), bad)
     assert torch.equal(lse == -float("inf"), bad)
     close(out[~bad].numpy(), plain[~bad.numpy()], *TOL["bf16"], cfg.name)
+
+
+def test_plans_of_earlier_libraries_keep_merging():
+    """A plan whose header does not count its narrow merge groups, and whose info
+    does not count merge workgroups, as libraries without wide groups wrote them,
+    gives the same result."""
+    _gpu()
+    from paper_2605_11232_amd.runtime import DeviceReplay
+    cfg = synth.AttnConfig("old-plan", "bf16", 32, 8, 128, 16, 6600)
+    dev = DeviceReplay(launch_workload(cfg, [1] * 3, [1000, 257, 2300], 62)).setup()
+    p = dev.prepare(dev.wl.launches[0])
+    dev.append(p)
+    dev.attend(p)
+    plain, plain_lse = p.out.clone(), p.lse.clone()
+    assert p.info.n_groups > 8
+    p.plan[28] = 0  # groups of at most four rows
+    p.info.n_merge_items = 0
+    p.out.zero_()
+    p.lse.zero_()
+    dev.attend(p)
+    torch.cuda.synchronize()
+    assert torch.equal(p.out, plain) and torch.equal(p.lse, plain_lse)

@@ -7,7 +7,7 @@ import pytest
 from paper_2605_11232_amd import binding as B
 from paper_2605_11232_amd import synth
 from paper_2605_11232_amd.runtime import plan_words_bound
-from tests.test_capi_host import H_N_GROUP_TMPL, check_plan
+from tests.test_capi_host import H_N_GROUP_TMPL, H_N_GROUPS, check_plan
 
 H_N_GROUP_NARROW = 28  # header word: merge groups of at most four rows
 
@@ -70,6 +70,21 @@ def test_decode_plans_keep_fitting_the_array_without_workspace():
                 assert info.workspace_bytes <= B.NOALLOC_WORKSPACE_BYTES
                 fits += 1
     assert fits > 5
+
+
+def test_plan_info_counts_merge_groups():
+    """n_groups is the number of groups the merge combines, whatever the number of
+    rows of a group, and the header's."""
+    wide = 0
+    for q, L in [([389], [2437]), ([100, 1], [4196, 900]), ([1, 1], [1000, 257]), ([40], [60])]:
+        plan, info = B.plan(B.KIND_PREFILL, 0, np.array(L), np.concatenate([[0], np.cumsum(q)]), 32, 8, 128, 16,
+                            B.PA_BF16, 256)
+        groups = plan[H_N_GROUP_TMPL] * 8
+        assert info.n_groups == plan[H_N_GROUPS] == groups
+        is_wide = plan[H_N_GROUP_NARROW] < plan[H_N_GROUP_TMPL]
+        assert (info.n_merge_items > groups) == is_wide
+        wide += is_wide
+    assert wide == 2
 
 
 @pytest.mark.parametrize("D", [64, 128])
