@@ -204,7 +204,8 @@ __device__ __forceinline__ void tile_item(const int32_t* it, int g, int poff, co
     hq = g * G + (rho - qi * G);
     part = it[I_PART] < 0 ? -1 : it[I_PART] + poff + lr;
     key_seq = r;
-    kend = min(it[I_KV1], L) - int(uint32_t(it[I_FLAGS]) / kItemPast);
+    // the range may run past the last key that the item's last row sees
+    kend = min(it[I_KV1], L - n + (row0 + nrows - 1) / G + 1);
     apos = valid ? L - n + qi : -1;
     // Rows are ordered by query, so the item's first row has the smallest
     // position: steps entirely at or below it need no causal mask.

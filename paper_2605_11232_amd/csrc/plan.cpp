@@ -532,8 +532,9 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
             tile_cost.push_back(int64_t(kv1) * nrows);
             continue;
           }
-          // equal key ranges covering [0, L), the last one marked with the keys
-          // past the tile's last row
+          // equal ranges of the keys the tile's rows see; the last one is recorded up to
+          // the sequence's end, so that the parts cover it (the kernel stops at the last
+          // row's key)
           const int32_t per = int32_t(cdiv(cdiv(kv1, nsplit), pa::kTileStep) * pa::kTileStep);
           const int32_t used = int32_t(cdiv(kv1, per));
           const int32_t base = int32_t(head_partial);
@@ -541,8 +542,7 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
           t_wide.push_back({r, 0, row0, nrows, used, base, nrows, 0});
           for (int32_t sp = 0; sp < used; ++sp) {
             const int32_t k0 = sp * per, k1 = std::min(kv1, k0 + per);
-            const int32_t past = sp + 1 == used ? L - kv1 : 0;
-            t_tiles.push_back({r, 0, row0, nrows, k0, k1 + past, base + sp * nrows, past * pa::kItemPast});
+            t_tiles.push_back({r, 0, row0, nrows, k0, sp + 1 == used ? L : k1, base + sp * nrows, 0});
             tile_cost.push_back(int64_t(k1 - k0) * nrows);
           }
         }

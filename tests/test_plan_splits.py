@@ -7,7 +7,7 @@ import pytest
 from paper_2605_11232_amd import binding as B
 from paper_2605_11232_amd import synth
 from paper_2605_11232_amd.runtime import plan_words_bound
-from tests.test_capi_host import H_N_GROUP_TMPL, H_N_GROUPS, check_plan
+from tests.test_capi_host import H_N_GROUP_TMPL, H_N_GROUPS, check_plan, parse_plan
 
 H_N_GROUP_NARROW = 28  # header word: merge groups of at most four rows
 
@@ -129,3 +129,14 @@ def test_launches_of_few_workgroups_have_no_tail_lists():
         plan, info = B.plan(B.KIND_PREFILL, 0, L, np.arange(n + 1) * 128, 32, 8, 128, 16, B.PA_BF16, 256)
         check_plan(plan, info, L, np.arange(n + 1) * 128, 4, 8, 128)
         assert bool(info.variant & 4) == tail
+
+
+def test_key_split_tiles_hold_plain_ranges():
+    """A key-split tile's item is what its words say: no flag but the streaming
+    one, the parts of a tile one after another from key 0 to the sequence's end."""
+    plan, info = B.plan(B.KIND_PREFILL, 0, np.array([4196, 3000]), np.array([0, 100, 165]), 28, 4, 128, 16,
+                        B.PA_BF16, 256)
+    tiles = parse_plan(plan)[2]
+    assert plan[H_N_GROUP_NARROW] == 0 and len(tiles) > 4 * plan[H_N_GROUP_TMPL]
+    assert {t[7] for t in tiles} == {0}
+    check_plan(plan, info, np.array([4196, 3000]), np.array([0, 100, 165]), 7, 4, 128)
