@@ -259,8 +259,7 @@ typedef struct pa_plan_info {
   int32_t n_merge_rows;    /* (token, head) rows produced by the merge step       */
   int32_t grid;            /* workgroups of the attention launch                  */
   int32_t variant;         /* kernel instantiation (internal)                     */
-  int32_t n_merge_items;   /* workgroups of the merge step, where it takes several
-                              per group (internal)                                */
+  int32_t n_merge_items;   /* workgroups of the merge launch                      */
   int64_t plan_words;      /* int32 words of the plan array                       */
   int64_t workspace_bytes; /* device scratch the attention call needs             */
   /* The launch shape the plan was built for; the attention calls reject a

@@ -13,7 +13,7 @@ int launch_attn_bf16(const void* q, const void* kc, const void* vc, int32_t num_
                      const int32_t* bt, int32_t max_blocks, const int32_t* seq_lens,
                      const int32_t* cu_q, int32_t hq, int32_t hkv, int32_t d, float scale,
                      const int32_t* plan, int32_t grid, int32_t n_tile, int32_t n_merge,
-                     bool wide_rows, bool tail, int64_t partial_rows, void* ws, void* out,
+                     int32_t merge_narrow, bool wide_rows, bool tail, int64_t partial_rows, void* ws, void* out,
                      float* lse, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
 int launch_attn_f32(const void* q, const void* kc, const void* vc, int32_t num_blocks,
                     const int32_t* bt, int32_t max_blocks, const int32_t* seq_lens,
@@ -130,10 +130,14 @@ int attn_common(const char* fn, int32_t want_kind, const void* q, const void* k_
                               head_dim, scale, out, lse, st, ev_start, ev_stop);
   } else {
     if (!plan) return fail(PA_ERR_ARG, "%s: NULL plan", fn);
-    const int32_t n_merge =
-        info->variant & kVariantWideGroups ? info->n_merge_items : info->n_groups;
-    if ((info->variant & ~(kVariantWideRows | kVariantTail | kVariantWideGroups)) != kVariantBf16 ||
+    // merge workgroups: one per narrow group, kWideGroupParts per wide one
+    const bool counted = (info->variant & kVariantMergeItems) != 0;
+    const int32_t n_merge = counted ? info->n_merge_items : info->n_groups;
+    const int32_t n_wide =
+        int32_t((int64_t(n_merge) - info->n_groups) / (kWideGroupParts - 1));
+    if ((info->variant & ~(kVariantWideRows | kVariantTail | kVariantMergeItems)) != kVariantBf16 ||
         info->grid < 0 || info->n_groups < 0 || n_merge < info->n_groups ||
+        n_wide > info->n_groups ||
         info->n_tile_items < 0 || info->n_shared_items < 0 ||
         int64_t(info->n_tile_items) + info->n_shared_items > info->grid ||
         info->partial_rows < 0 ||
@@ -162,7 +166,8 @@ int attn_common(const char* fn, int32_t want_kind, const void* q, const void* k_
     rc = dev::launch_attn_bf16(q, k_cache, v_cache, num_blocks, block_table, max_blocks_per_seq,
                                seq_lens, cu_seqlens_q, num_q_heads, num_kv_heads, head_dim, scale,
                                plan, info->grid, info->n_shared_items + info->n_tile_items,
-                               n_merge, (info->variant & kVariantWideRows) != 0,
+                               n_merge,
+                               counted ? (info->n_groups - n_wide) / num_kv_heads : -1, (info->variant & kVariantWideRows) != 0,
                                (info->variant & kVariantTail) != 0,
                                partial_rows,
                                workspace, out, lse, st, ev_start, ev_stop);

@@ -53,6 +53,7 @@ struct AttnArgs {
   int32_t hq;
   int32_t hkv;
   int32_t group;
+  int32_t merge_narrow;  // narrow merge-group templates, or -1: as the plan says
   float scale_log2;
 };
 
@@ -875,8 +876,11 @@ __global__ __launch_bounds__(kMergeRows * 32) void merge_kernel(AttnArgs a) {
   constexpr int VD = D / 32;  // output dims per lane
   constexpr int C = 16;       // parts whose loads are in flight together
   typedef float vecf __attribute__((ext_vector_type(VD)));
-  const int n_tmpl = a.plan[H_N_GROUP_TMPL];
-  const int narrow = int(gridDim.x) == n_tmpl ? n_tmpl : a.plan[H_N_GROUP_NARROW];
+  int narrow = a.merge_narrow;
+  if (narrow < 0) {  // an earlier library's plan
+    const int n_tmpl = a.plan[H_N_GROUP_TMPL];
+    narrow = int(gridDim.x) == n_tmpl ? n_tmpl : a.plan[H_N_GROUP_NARROW];
+  }
   const int g = blockIdx.y;
   int t = blockIdx.x, sub = 0;  // template, and which of its rows
   if (t >= narrow) {
@@ -911,38 +915,31 @@ __global__ __launch_bounds__(kMergeRows * 32) void merge_kernel(AttnArgs a) {
   for (int s = 32 + lane; s - lane < nsplit; s += 32) mx = fmaxf(mx, s < nsplit ? part_lse(s) : kNegInf);
 #pragma unroll
   for (int o = 16; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+  // Without any finite part both references are 0: all weights are then zero, and
+  // the row is zeros, or NaN where the parts hold it.
+  const bool none = mx == kNegInf;
+  const float ref = none ? 0.f : mx;
+  float sum = exp2f((lse0 - ref) * kLog2e);
+  for (int s = 32 + lane; s - lane < nsplit; s += 32)
+    if (s < nsplit) sum += exp2f((part_lse(s) - ref) * kLog2e);
+#pragma unroll
+  for (int o = 16; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  const float lse_v = ref + kLn2 * __log2f(sum);
+  const float wref = none ? 0.f : lse_v;
   vecf o_acc = {};
-  float lse_v = kNegInf;
-  if (mx == kNegInf) {
-    // no part has a sum above zero: zeros, or NaN where the parts hold it (a
-    // row without a finite score must not come out as zeros)
-    for (int s0 = 0; s0 < nsplit; s0 += C) {
-      if (s0 > 0) load_batch(s0);
-#pragma unroll
-      for (int u = 0; u < C; ++u)
-        if (s0 + u < nsplit) o_acc += 0.f * x[u];
-    }
-  } else {
-    float sum = lse0 == kNegInf ? 0.f : exp2f((lse0 - mx) * kLog2e);
-    for (int s = 32 + lane; s - lane < nsplit; s += 32)
-      if (s < nsplit) sum += exp2f((part_lse(s) - mx) * kLog2e);
-#pragma unroll
-    for (int o = 16; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, 64);
-    lse_v = mx + kLn2 * __log2f(sum);
-    // weight of part s0 + lane of the current round of 32, held by that lane
-    float wl = exp2f((lse0 - lse_v) * kLog2e);
-    for (int s0 = 0; s0 < nsplit; s0 += C) {
-      if (s0 > 0) {
-        load_batch(s0);
-        if (s0 % 32 == 0) {
-          const int s = s0 + lane;
-          wl = s < nsplit ? exp2f((part_lse(s) - lse_v) * kLog2e) : 0.f;
-        }
+  // weight of part s0 + lane of the current round of 32, held by that lane
+  float wl = exp2f((lse0 - wref) * kLog2e);
+  for (int s0 = 0; s0 < nsplit; s0 += C) {
+    if (s0 > 0) {
+      load_batch(s0);
+      if (s0 % 32 == 0) {
+        const int s = s0 + lane;
+        wl = s < nsplit ? exp2f((part_lse(s) - wref) * kLog2e) : 0.f;
       }
-#pragma unroll
-      for (int u = 0; u < C; ++u)
-        if (s0 + u < nsplit) o_acc += __shfl(wl, half | ((s0 + u) & 31), 64) * x[u];
     }
+#pragma unroll
+    for (int u = 0; u < C; ++u)
+      if (s0 + u < nsplit) o_acc += __shfl(wl, half | ((s0 + u) & 31), 64) * x[u];
   }
   if (!valid) return;
   const int qs = a.cu_q[r];
@@ -965,7 +962,7 @@ int launch_attn_bf16(const void* q, const void* kc, const void* vc, int32_t num_
                      const int32_t* bt, int32_t max_blocks, const int32_t* seq_lens,
                      const int32_t* cu_q, int32_t hq, int32_t hkv, int32_t d, float scale,
                      const int32_t* plan, int32_t grid, int32_t n_tile, int32_t n_merge,
-                     bool wide_rows, bool tail, int64_t partial_rows, void* ws, void* out,
+                     int32_t merge_narrow, bool wide_rows, bool tail, int64_t partial_rows, void* ws, void* out,
                      float* lse, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
   AttnArgs a;
   a.q = static_cast<const __bf16*>(q);
@@ -984,6 +981,7 @@ int launch_attn_bf16(const void* q, const void* kc, const void* vc, int32_t num_
   a.hq = hq;
   a.hkv = hkv;
   a.group = hq / hkv;
+  a.merge_narrow = merge_narrow;
   a.scale_log2 = scale * kLog2e;
   if (grid > 0) {
     // tiles and rows together: the tile path's register budget holds the

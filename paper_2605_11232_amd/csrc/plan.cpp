@@ -751,7 +751,7 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
   info->variant = dtype == PA_F32 ? 0
                                   : (pa::kVariantBf16 | (wide ? pa::kVariantWideRows : 0) |
                                      (n_tail ? pa::kVariantTail : 0) |
-                                     (t_wide.empty() ? 0 : pa::kVariantWideGroups));
+                                     pa::kVariantMergeItems);
   info->plan_words = words;
   info->workspace_bytes = partial_rows * int64_t(head_dim + 1) * int64_t(sizeof(float));
   info->n_seqs = n_seqs;

@@ -20,8 +20,9 @@ constexpr int32_t kPlanMagic = 0x31304150;  // "PA01"
 // write the partial rows of head 0's template plus g * HEAD_PARTIAL.  The
 // merge launch has, per kv-head, one workgroup for each of the first
 // N_GROUP_NARROW group templates and kWideGroupParts for each of the others;
-// as many workgroups as templates: all of them are narrow (plans of libraries
-// without wide groups have no N_GROUP_NARROW, the word is zero).
+// the kernel takes their number from pa_plan_info.  With an earlier library's
+// info it takes N_GROUP_NARROW, which is zero in the oldest plans: those have as
+// many merge workgroups as templates, all of them narrow.
 enum : int32_t {
   H_MAGIC = 0,
   H_KIND,
@@ -111,11 +112,11 @@ enum : int32_t {
 // pa_plan_info.variant: 0 float32 kernel; bf16 plans 1, plus 2 when some
 // row item holds more than 16 rows (selects the wide row-item kernel), plus 4
 // when the plan has tail lists (selects a kernel with wildcard workgroups),
-// plus 8 when it has wide merge groups (pa_plan_info.n_merge_items is set).
+// plus 8: pa_plan_info.n_merge_items is set (not so by earlier libraries).
 constexpr int32_t kVariantBf16 = 1;
 constexpr int32_t kVariantWideRows = 2;
 constexpr int32_t kVariantTail = 4;
-constexpr int32_t kVariantWideGroups = 8;
+constexpr int32_t kVariantMergeItems = 8;
 
 constexpr int32_t kTileRows = 128;    // rows per tile item (4 waves x 32)
 constexpr int32_t kRowItemRows = 32;  // rows per single-wave item (two 16-column MFMA tiles)
