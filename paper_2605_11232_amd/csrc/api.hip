@@ -18,8 +18,8 @@ int launch_attn_bf16(const void* q, const void* kc, const void* vc, int32_t num_
 int launch_attn_f32(const void* q, const void* kc, const void* vc, int32_t num_blocks,
                     const int32_t* bt, int32_t max_blocks, const int32_t* seq_lens,
                     const int32_t* cu_q, int32_t n_seqs, int32_t total_q, int32_t hq, int32_t hkv,
-                    int32_t d, float scale, void* out, float* lse, hipStream_t stream,
-                    hipEvent_t ev_start, hipEvent_t ev_stop);
+                    int32_t d, bool by_row, float scale, void* out, float* lse,
+                    hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
 int launch_kv_append(const void* kn, const void* vn, const int32_t* slots, int32_t n, void* kc,
                      void* vc, int32_t nb, int32_t hkv, int32_t d, int32_t dtype,
                      hipStream_t stream);
@@ -127,7 +127,8 @@ int attn_common(const char* fn, int32_t want_kind, const void* q, const void* k_
   if (dtype == PA_F32) {
     rc = dev::launch_attn_f32(q, k_cache, v_cache, num_blocks, block_table, max_blocks_per_seq,
                               seq_lens, cu_seqlens_q, n_seqs, total_q, num_q_heads, num_kv_heads,
-                              head_dim, scale, out, lse, st, ev_start, ev_stop);
+                              head_dim, info->variant == kVariantF32ByRow, scale, out, lse, st,
+                              ev_start, ev_stop);
   } else {
     if (!plan) return fail(PA_ERR_ARG, "%s: NULL plan", fn);
     // merge workgroups: one per narrow group, kWideGroupParts per wide one

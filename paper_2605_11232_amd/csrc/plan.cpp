@@ -214,6 +214,32 @@ int64_t tile_split_keys(int32_t n_seqs, const int32_t* seq_lens, const int32_t* 
   return best_keys;
 }
 
+// float32: one wavefront per (token, head) instead of tiles of 16 rows.  The
+// tiles' chain of loads and their mostly empty matrix instructions cost more
+// where every sequence has one row (or two) per kv-head, few keys, and there are
+// so many that the chip is full either way.  us by row and by tiles: 32/32 heads
+// of 64, one token each, 64 sequences of 40 keys 9.9 and 14.6, of 100 18.8 and
+// 22.0, of 150 25.7 and 28.8, 256 of 200-300 196 and 188; of 128, 64 of 64 keys 24
+// and 29, 128 of 100 94 and 87; two tokens each, heads of 64, 400 of 40 keys 69 and
+// 89, of 64 115 and 105 (of 128, 40 keys 173 and 159); 32/16 heads of 128 (two rows), 400 of 16 keys 35 and 47, of
+// 40 91 and 79; 32/8 heads, 400 of 16 21 and 16; 16 sequences of 32/32 heads, 40
+// keys, 9.3 and 6.4.
+bool f32_by_row(int32_t n_seqs, const int32_t* seq_lens, const int32_t* cu, int32_t hq, int32_t hkv,
+                int32_t head_dim, int32_t num_cus) {
+  const int32_t G = hq / hkv;
+  if (G > 2) return false;
+  int64_t seqs = 0, rows = 0, keys = 0;
+  for (int32_t r = 0; r < n_seqs; ++r) {
+    const int64_t n = cu[r + 1] - cu[r];
+    if (n == 0) continue;
+    ++seqs;
+    rows = std::max(rows, n * G);
+    keys = std::max<int64_t>(keys, seq_lens[r]);
+  }
+  const int64_t most_keys = rows == 1 ? (head_dim == 64 ? 144 : 64) : G == 1 && head_dim == 64 ? 48 : 32;
+  return rows <= 2 && keys <= most_keys && seqs * hkv >= 8 * int64_t(num_cus);
+}
+
 }  // namespace
 
 extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int32_t* seq_lens,
@@ -714,8 +740,12 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
   const int64_t n_merge = (n_narrow + int64_t(t_wide.size()) * pa::kWideGroupParts) * num_kv_heads;
   t_groups.insert(t_groups.end(), t_wide.begin(), t_wide.end());
   const int64_t head_members = int64_t(t_members.size());
-  const int64_t grid = dtype == PA_F32 ? int64_t(total_q) * num_q_heads
-                                       : int64_t(dispatch.size());
+  const bool by_row = dtype == PA_F32 && f32_by_row(n_seqs, seq_lens, cu_seqlens_q, num_q_heads,
+                                                    num_kv_heads, head_dim, num_cus);
+  const int64_t f32_rows = int64_t(total_q) * num_q_heads;
+  const int64_t grid = dtype != PA_F32 ? int64_t(dispatch.size())
+                       : by_row || total_q == 0 ? f32_rows
+                       : pa::f32_tile_grid(total_q, n_seqs, num_q_heads, num_kv_heads);
   // layout: header, dispatch list, tail table and lists, counters,
   // templates (shared, tile, row, group), member table
   const int64_t dispatch_off = pa::kHeaderWords;
@@ -733,7 +763,8 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
       (num_kv_heads >= (1 << (31 - pa::kDispatchHeadShift)) ||
        t_shared.size() + t_tiles.size() + sorted_rows.size() >= size_t(pa::kWildcard)))
     return pa::fail(PA_ERR_ARG, "pa_attn_plan: launch too large");
-  if (words >= (int64_t{1} << 31) || grid >= (int64_t{1} << 31) || partial_rows >= (int64_t{1} << 31))
+  if (words >= (int64_t{1} << 31) || grid >= (int64_t{1} << 31) || partial_rows >= (int64_t{1} << 31) ||
+      (dtype == PA_F32 && f32_rows >= (int64_t{1} << 31)))
     return pa::fail(PA_ERR_ARG, "pa_attn_plan: launch too large");
 
   info->kind = kind;
@@ -748,7 +779,7 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
   info->grid = int32_t(grid);
   bool wide = false;
   for (const auto& it : t_rows) wide = wide || it[pa::I_NROWS] > 16;
-  info->variant = dtype == PA_F32 ? 0
+  info->variant = dtype == PA_F32 ? (by_row ? pa::kVariantF32ByRow : 0)
                                   : (pa::kVariantBf16 | (wide ? pa::kVariantWideRows : 0) |
                                      (n_tail ? pa::kVariantTail : 0) |
                                      pa::kVariantMergeItems);

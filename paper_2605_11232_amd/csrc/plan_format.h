@@ -117,6 +117,8 @@ constexpr int32_t kVariantBf16 = 1;
 constexpr int32_t kVariantWideRows = 2;
 constexpr int32_t kVariantTail = 4;
 constexpr int32_t kVariantMergeItems = 8;
+// float32: the kernel of one wavefront per (token, head) instead of row tiles.
+constexpr int32_t kVariantF32ByRow = 16;
 
 constexpr int32_t kTileRows = 128;    // rows per tile item (4 waves x 32)
 constexpr int32_t kRowItemRows = 32;  // rows per single-wave item (two 16-column MFMA tiles)
@@ -128,5 +130,22 @@ constexpr int32_t kRowItemBlocks = 64;  // most blocks (of 16 keys) one row item
 constexpr int32_t kTileStep = 64;     // keys per tile-item inner iteration
 constexpr int32_t kSharedChunk = 6144;  // most shared keys one cascade item covers
 constexpr int32_t kSharedMinKeys = 256; // shorter shared prefixes are not split off
+
+// float32 row tiles (no work items: the kernel finds its rows in cu_seqlens_q).
+// 32 rows per workgroup read half the keys per row of 16, but leave two
+// wavefronts per SIMD instead of three and half as many workgroups: used once
+// two of them per compute unit remain (8 requests of 512-1024 new tokens,
+// 32/8 heads, 0.96 against 1.10 ms; 360 workgroups 47 against 40 us; 380 and
+// 760 even) and sequences have rows to fill them (a decode token has G).
+inline bool f32_wide_tiles(int64_t total_q, int64_t n_seqs, int32_t hq, int32_t hkv) {
+  const int64_t rows = total_q * (hq / hkv);  // of one kv-head
+  return rows / 32 * hkv >= 512 && rows >= 32 * n_seqs;
+}
+// Workgroups: tiles of one kv-head, at most one more per sequence than its rows
+// fill, times kv-heads.
+inline int64_t f32_tile_grid(int64_t total_q, int64_t n_seqs, int32_t hq, int32_t hkv) {
+  const int64_t tile_rows = f32_wide_tiles(total_q, n_seqs, hq, hkv) ? 32 : 16;
+  return (total_q * (hq / hkv) / tile_rows + n_seqs) * hkv;
+}
 
 }  // namespace pa

@@ -66,7 +66,13 @@ F32 = [
     (8, 2, 128, [2, 1], [4200, 4097]),
     (32, 32, 64, [520, 9], [600, 31]),
     (32, 8, 128, [300, 230, 0], [317, 530, 64]),
+    # one wavefront per (token, head): one row per kv-head, two by tokens and by heads
+    (32, 32, 64, [1] * 70 + [0], [1 + 2 * i for i in range(70)] + [40]),
+    (32, 32, 128, [1] * 70, [64 - i % 17 for i in range(70)]),
+    (32, 32, 64, [2, 1] * 35, [48 - i % 46 for i in range(70)]),
+    (32, 16, 128, [1] * 130, [1 + i % 32 for i in range(130)]),
 ]
+F32_BY_ROW = 4  # of them, the last
 
 
 @pytest.mark.parametrize("case", range(len(F32)))
@@ -74,8 +80,9 @@ def test_f32_tiles(case):
     _gpu()
     hq, hkv, d, q_lens, lens = F32[case]
     cfg = synth.AttnConfig(f"f32-{case}", "f32", hq, hkv, d, 16, 6100 + case)
-    errs, _, _ = run_parity(launch_workload(cfg, q_lens, lens, 40 + case), label=cfg.name)
+    errs, dev, _ = run_parity(launch_workload(cfg, q_lens, lens, 40 + case), label=cfg.name)
     say(f"{cfg.name} normalized errors", errs)
+    assert (dev.infos[0].variant == 16) == (case >= len(F32) - F32_BY_ROW)
 
 
 def test_f32_values_that_are_not_finite_stay_with_their_rows():

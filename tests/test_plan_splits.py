@@ -140,3 +140,36 @@ def test_key_split_tiles_hold_plain_ranges():
     assert plan[H_N_GROUP_NARROW] == 0 and len(tiles) > 4 * plan[H_N_GROUP_TMPL]
     assert {t[7] for t in tiles} == {0}
     check_plan(plan, info, np.array([4196, 3000]), np.array([0, 100, 165]), 7, 4, 128)
+
+
+def _f32(hq, hkv, d, q, L):
+    _, info = B.plan(B.KIND_PREFILL, 0, np.array(L), np.concatenate([[0], np.cumsum(q)]), hq, hkv, d, 16, B.PA_F32, 256)
+    assert info.workspace_bytes == 0 and info.n_groups == 0
+    return info
+
+
+def test_float32_plans_count_their_workgroups():
+    """Row tiles: 16 or 32 rows of a sequence and kv-head to a workgroup, at most one
+    workgroup more per sequence than its rows fill."""
+    for hq, hkv, q, tile in [(8, 2, [40, 3, 0], 16), (32, 8, [64] * 16, 32), (32, 8, [500, 530], 32), (28, 4, [1] * 9, 16)]:
+        info = _f32(hq, hkv, 128, q, [x + 100 for x in q])
+        rows = np.array(q) * (hq // hkv)
+        assert info.variant == 0
+        assert sum(-(-rows // tile)) * hkv <= info.grid <= (sum(rows) // tile + len(q)) * hkv
+
+
+def test_float32_short_sequences_of_one_row_run_by_row():
+    """One wavefront per (token, head) where every sequence has one row per kv-head (or
+    two), few keys, and the chip is full; a single longer or taller one: tiles."""
+    for hq, hkv, d, q, L, by_row in [
+            (32, 32, 64, [1] * 64, [144] * 64, True), (32, 32, 64, [1] * 64, [144] * 63 + [145], False),
+            (32, 32, 128, [1] * 64, [64] * 64, True), (32, 32, 128, [1] * 64, [65] * 64, False),
+            (32, 32, 64, [1] * 63, [20] * 63, False), (32, 32, 64, [1] * 64 + [0], [20] * 64 + [500], True),
+            (32, 16, 64, [1] * 128, [32] * 128, True), (32, 16, 64, [1] * 128, [33] * 128, False),
+            (32, 32, 64, [2] * 64, [48] * 64, True), (32, 32, 64, [2] * 64, [49] * 64, False),
+            (32, 32, 128, [2] * 64, [33] * 64, False), (32, 32, 64, [3] + [1] * 70, [20] * 71, False),
+            (32, 8, 64, [1] * 400, [4] * 400, False)]:
+        info = _f32(hq, hkv, d, q, L)
+        assert (info.variant == 16) == by_row
+        if by_row:
+            assert info.grid == sum(q) * hq
