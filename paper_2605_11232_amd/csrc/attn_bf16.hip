@@ -193,7 +193,7 @@ __device__ __forceinline__ void tile_item(const int32_t* it, int g, int poff, co
     part = mem[1] + poff + rl;
     key_seq = it[S_BLOCK_SEQ];
     kend = it[S_KV1];
-    apos = valid ? kend - 1 : -1;  // every shared key is visible
+    apos = kend - 1;               // every shared key is visible
     wg_amin = kend - 1;            // only a partial last step is masked
   } else {
     const int r = it[I_SEQ];
@@ -207,7 +207,9 @@ __device__ __forceinline__ void tile_item(const int32_t* it, int g, int poff, co
     key_seq = r;
     // the range may run past the last key that the item's last row sees
     kend = min(it[I_KV1], L - n + (row0 + nrows - 1) / G + 1);
-    apos = valid ? L - n + qi : -1;
+    // Lanes without a row see every key (their scores are zero): seeing none they would
+    // never have a reference, and the wavefront would look for one in each masked step.
+    apos = valid ? L - n + qi : kend - 1;
     // Rows are ordered by query, so the item's first row has the smallest
     // position: steps entirely at or below it need no causal mask.
     wg_amin = L - n + row0 / G;
