@@ -52,10 +52,15 @@ constexpr int64_t kPrivateTileKeys = 4160;  // most private keys a few-row tile 
 constexpr int64_t kMinTileKeys = 256;       // fewest, in launches that leave compute units idle
 constexpr int64_t kMinRowKeys = 256;        // split target floor of row items
 // Fewest keys a row item is split down to in a launch without long sequences'
-// tiles (beside those the rows are not what it waits for), while the sequence's
-// part count stays within the workspace bound: 4 decode requests on a
-// 2048-token prefix 19.4 us per append and call against 20.7 with 256 (128: even).
-constexpr int64_t kPlanRowKeys = 192;
+// tiles (beside those the rows are not what it waits for) that comes to at most
+// kSmallRowWavesPerCu such items per CU, while the sequence's part count stays
+// within the workspace bound: 4 decode requests on a 2048-token prefix 19.4 us per
+// append and call against 20.7 with 256 (128: even).  More of them no longer find a
+// compute unit each and only cost more parts: 48 requests of 460-1536 keys past 512
+// shared ones, 28/4 heads (1088 items against 896) 24.6 us and 21.5, 93 of them past
+// 992 43.2 and 40.1, 48 of 32/8 heads 41.0 and 37.3.
+constexpr int64_t kSmallRowKeys = 192;
+constexpr int64_t kSmallRowWavesPerCu = 3;
 constexpr int64_t kSplitKeys = 256;         // fewest keys of a part of a key-split tile
 constexpr int64_t kTailWorkPct = 10;        // row work given half-length items (per cent)
 constexpr int64_t kStealPct = 5;            // tile work in the tail list (per cent)
@@ -427,7 +432,9 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
       return std::max<int64_t>(1, std::min(cdiv(len, on_tiles(r) ? tile_keys : row_chunk[r]), most));
     };
     for (int32_t S : cg_keys) cg_chunks.push_back(int32_t(cdiv(S, pa::kSharedChunk)));
-    split_rows(long_seqs ? kMinRowKeys : kPlanRowKeys);
+    const bool small_rows =
+        !long_seqs && cdiv(row_keys, kSmallRowKeys) <= kSmallRowWavesPerCu * num_cus;
+    split_rows(small_rows ? kSmallRowKeys : kMinRowKeys);
 
     // Key chunks of the shared prefixes.  A shared item is a serial walk over
     // its keys, so in a launch with little else to do few long chunks leave
@@ -451,7 +458,11 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
         const int64_t keys = seq_lens[r] - kstart[r];
         if (is_row(r)) {
           rest += double(keys) * num_kv_heads * head_dim * 4 / kStepBytes;
-          longest = std::max(longest, (on_tiles(r) ? 1 : 2) * cdiv(keys, private_parts(r)));
+          int64_t per = cdiv(keys, private_parts(r));
+          // rows of the usual length as of the small launches' (992 shared keys in two
+          // chunks beside them: 64 requests of 240-800 keys, 32/8 heads, 29 us and 34)
+          if (!on_tiles(r)) per = 2 * (per <= kMinRowKeys ? std::min(per, kSmallRowKeys) : per);
+          longest = std::max(longest, per);
         } else {
           rest += 4.0 * head_dim * qlen(r) * num_q_heads * double(keys) / kStepFlops;
         }
