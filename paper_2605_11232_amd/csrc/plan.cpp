@@ -438,7 +438,7 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
 
     // Key chunks of the shared prefixes.  A shared item is a serial walk over
     // its keys, so in a launch with little else to do few long chunks leave
-    // the chip waiting for them.  Chunks are cut until an item takes a third of
+    // the chip waiting for them.  Chunks are cut until an item takes two fifths of
     // what the rest of the launch takes (its steps run slower beside that; kStep*:
     // what the whole chip does during one 64-key step) or about as long as the
     // longest private item (a row item's 32-key step takes about as long as
@@ -446,9 +446,12 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
     // workgroup per CU.  Append and call, us, whole and cut: 4 decode requests of
     // 256-1152 keys of their own on a 2048-token prefix, 32/8 heads, 42 and 19; 64 of
     // them 65 and 48; 128 on 8192 tokens 119 and 85; 64 of 100-300 on 8192,
-    // 28/4 heads, 84 and 32; 16 verifications of 5 tokens on 4096 84 and 34.  A half
-    // or a sixth instead of a third: up to 12 % slower.  256 decode requests have
-    // enough private work (143 us, one chunk either way).
+    // 28/4 heads, 84 and 32; 16 verifications of 5 tokens on 4096 84 and 34.  256
+    // decode requests have enough private work (143 us, one chunk either way).  A
+    // third cuts chunks that nothing waits for (a 512-token prefill chunk beside 48
+    // decode requests on 1024 shared keys, 64/8 heads, 41.2 us, 38.4 whole; two fifths
+    // leaves it whole), a half leaves some that are (160 decode requests on 4096, 32/8
+    // heads, 130 against 119).
     if (!cg_keys.empty()) {
       constexpr double kStepBytes = 6.6e6, kStepFlops = 1.2e9;  // 1.2 us at 5.5 TB/s, 1 PFLOP/s
       double rest = 0;      // steps
@@ -473,9 +476,9 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
         row_tiles += cdiv(members * qlen(cg_seqs[cg_begin[c]]) * G, pa::kTileRows);
       }
       longest = std::max<int64_t>(longest, pa::kSharedMinKeys);
-      const int64_t third = 1 + int64_t(std::min(rest, 1e6) / 3 * pa::kTileStep);
+      const int64_t share = 1 + int64_t(std::min(rest, 1e6) * 0.4 * pa::kTileStep);
       for (size_t c = 0; c < cg_keys.size(); ++c) {
-        const int64_t n = std::min<int64_t>({cg_keys[c] / longest, (cg_keys[c] + third / 2) / third,
+        const int64_t n = std::min<int64_t>({cg_keys[c] / longest, (cg_keys[c] + share / 2) / share,
                                              num_cus / (row_tiles * num_kv_heads)});
         cg_chunks[c] = int32_t(std::max<int64_t>(cg_chunks[c], n));
       }

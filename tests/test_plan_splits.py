@@ -115,6 +115,22 @@ def test_row_items_are_split_finer_only_where_they_leave_the_chip_room():
         assert max(t[5] - t[4] for t in parse_plan(plan)[3] if t[0] >= 0) == most
 
 
+def test_prefix_chunks_beside_enough_other_work_stay_whole():
+    """1024 shared keys of 48 decode requests: two chunks in a launch of their own, one
+    beside a 512-token prefill chunk, whose steps they run beside."""
+    for chunk, chunks in [(0, 2), (512, 1)]:
+        q = np.array([chunk] * (chunk > 0) + [1] * 48)
+        L = np.array([chunk] * (chunk > 0) + [1024 + 704] * 48)
+        cu = np.concatenate([[0], np.cumsum(q)])
+        bt = _tables(None, L, 1024)
+        if chunk:
+            bt[0] = -1
+            bt[0, :32] = np.arange(32) + 5 * 10 ** 7
+        plan, info = B.plan(B.KIND_PREFILL, 0, L, cu, 64, 8, 128, 16, B.PA_BF16, 256, block_table=bt)
+        check_plan(plan, info, L, cu, 8, 8, 128)
+        assert info.n_shared_items == chunks * 3 * 8
+
+
 def test_few_row_tiles_fill_idle_compute_units():
     """33 to 64 rows per sequence: a launch that leaves compute units idle gets more
     items, one per compute unit at most; one key range of up to 512 keys that needs
