@@ -61,6 +61,9 @@ constexpr int64_t kMinRowKeys = 256;        // split target floor of row items
 // 992 43.2 and 40.1, 48 of 32/8 heads 41.0 and 37.3.
 constexpr int64_t kSmallRowKeys = 192;
 constexpr int64_t kSmallRowWavesPerCu = 3;
+// What the whole chip does during one 64-key step of a tile: 1.2 us at 5.5 TB/s,
+// 1 PFLOP/s.
+constexpr double kStepBytes = 6.6e6, kStepFlops = 1.2e9;
 constexpr int64_t kSplitKeys = 256;         // fewest keys of a part of a key-split tile
 constexpr int64_t kTailWorkPct = 10;        // row work given half-length items (per cent)
 constexpr int64_t kStealPct = 5;            // tile work in the tail list (per cent)
@@ -219,6 +222,52 @@ int64_t tile_split_keys(int32_t n_seqs, const int32_t* seq_lens, const int32_t* 
   return best_keys;
 }
 
+// Private keys per tile item of the few-row sequences (33 to 64 rows): the fewest
+// of which an item still comes to one for each free compute unit, or
+// kPrivateTileKeys.  An item walks its keys in series; the split pays where the
+// steps it saves take longer than the merge it needs (unless the launch has one),
+// and not beside row items that take twice as long as the longest item anyway (four
+// times where an XCD has several, as they start spread over the row items).  A
+// step takes about a microsecond (head_dim 64 two thirds), 5 % more beyond one item
+// on every other CU, the merge 3.5 (2.7) plus the parts at 4.5 TB/s.
+// Call, us, whole and split: one verification of 5 tokens on 900 keys, 64/8 heads, 20
+// and 12, four on 467-700 15.3 and 12.9, 16 of them even, 31 (248 items, where one
+// sequence alone could be split) 17.6 and 19.0; 27 decode requests of 180-600 keys,
+// 96/2 heads of 64, 11.5 and 13.6 where only those above 512 were split; 32 on 4100
+// fill the chip.  Beside 256 decode requests (32/8 heads) one of 12 tokens on 1324 keys
+// 133 and 138, on 7000 172 and 149, four on 2000 159 and 149, on 300 139 and 141.
+struct FewTile {
+  int64_t keys, rows;
+};
+int64_t few_tile_keys(const std::vector<FewTile>& few, int32_t hkv, int32_t head_dim, int32_t num_cus,
+                      int64_t free_cus, double row_steps, bool other_merge) {
+  auto items = [&](int64_t keys) {
+    int64_t n = 0;
+    for (const auto& f : few) n += cdiv(f.keys, keys) * hkv;
+    return n;
+  };
+  int64_t longest = 0;
+  for (const auto& f : few) longest = std::max(longest, f.keys);
+  const double room = items(kPrivateTileKeys) > kXcds ? row_steps / 2 : row_steps;
+  if (items(kPrivateTileKeys) >= free_cus || (!other_merge && longest <= 2 * kMinTileKeys) ||
+      2 * double(cdiv(longest, pa::kTileStep)) <= room)
+    return kPrivateTileKeys;
+  auto estimate = [&](int64_t keys) {
+    int64_t steps = 0, partial_rows = 0;
+    for (const auto& f : few) {
+      const int64_t n = cdiv(f.keys, keys);
+      steps = std::max(steps, cdiv(cdiv(f.keys, n), pa::kTileStep));
+      if (n > 1) partial_rows += n * f.rows * hkv;
+    }
+    const double step = (head_dim == 64 ? 0.65 : 1) * (2 * items(keys) > num_cus ? 1.05 : 1);
+    const double merge = partial_rows == 0 || other_merge ? 0 : head_dim == 64 ? 2.7 : 3.5;
+    return double(steps) * step + merge + double(partial_rows) * (head_dim + 1) * 4 / 4.5e6;
+  };
+  int64_t keys = kMinTileKeys;
+  while (items(keys) > free_cus) keys += pa::kTileStep;
+  return estimate(keys) < estimate(kPrivateTileKeys) ? keys : kPrivateTileKeys;
+}
+
 // float32: one wavefront per (token, head) instead of tiles of 16 rows.  The
 // tiles' chain of loads and their mostly empty matrix instructions cost more
 // where every sequence has one row (or two) per kv-head, few keys, and there are
@@ -368,35 +417,28 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
     // aim for enough single-wave items to keep kRowWavesPerCu wavefronts per
     // CU busy, a split target of at least kMinRowKeys and at most 1024 keys
     // per item (halved for the tail below).
-    int64_t row_keys = 0, long_tiles = 0;
-    std::vector<int64_t> few_tile_keys;  // private keys of the sequences on_tiles
+    int64_t row_keys = 0, long_tiles = 0, longest_row = 0;
+    std::vector<FewTile> few;  // sequences on_tiles: private keys, rows
     for (int32_t r = 0; r < n_seqs; ++r) {
       const int64_t keys = seq_lens[r] - kstart[r];
       if (!is_row(r)) long_tiles += cdiv(int64_t(qlen(r)) * G, pa::kTileRows) * num_kv_heads;
-      else if (on_tiles(r)) few_tile_keys.push_back(keys);
-      else row_keys += keys * num_kv_heads;
+      else if (on_tiles(r)) few.push_back({keys, int64_t(qlen(r)) * G});
+      else row_keys += keys * num_kv_heads, longest_row = std::max(longest_row, keys);
     }
     const bool long_seqs = long_tiles > 0;
-    // Private keys per tile item of a few-row sequence (33 to 64 rows).  An item
-    // walks its keys in series, so a launch that leaves compute units idle gets
-    // the shortest items that still come to one for each CU without a tile of a
-    // long sequence.  Append and call, us, of one item per sequence and of
-    // these: one verification of 6 tokens on 1800 keys, 64/8 heads, 33 and 14; 5 on
-    // 3000-3500 past a prefix, 28/4 heads, 63 and 23; 8 on 6000-9000 83 and 52;
-    // 32 on 4100 fill the chip and stay whole.  So do items beside a shared prefix of
-    // several coarse chunks, where the chunk and item counts are fixed by the plan's
-    // contract (4 verifications of 5 tokens on 16384 shared and 4096 private keys: 3
-    // chunks, one private item each, 101 us; splitting both would take 41).
+    // what the row items take, in steps of the whole chip
+    const double row_steps = double(row_keys) * head_dim * 4 / kStepBytes;
     int64_t longest_prefix = 0;
     for (int32_t S : cg_keys) longest_prefix = std::max<int64_t>(longest_prefix, S);
-    int64_t tile_keys = kPrivateTileKeys;
-    auto tile_items = [&](int64_t keys) {
-      int64_t n = 0;
-      for (int64_t k : few_tile_keys) n += cdiv(k, keys) * num_kv_heads;
-      return n;
-    };
-    if (longest_prefix <= pa::kSharedChunk && tile_items(kPrivateTileKeys) < num_cus - long_tiles)
-      for (tile_keys = kMinTileKeys; tile_items(tile_keys) > num_cus - long_tiles;) tile_keys += pa::kTileStep;
+    // Beside a shared prefix of several coarse chunks the items stay whole, as the
+    // chunks and items of such launches are pinned by their tests (4 verifications of 5
+    // tokens on 16384 shared and 4096 private keys: 3 chunks, one private item each, 101
+    // us; splitting both would take 41).
+    const int64_t tile_keys =
+        longest_prefix > pa::kSharedChunk
+            ? kPrivateTileKeys
+            : few_tile_keys(few, num_kv_heads, head_dim, num_cus, num_cus - long_tiles, row_steps,
+                            !cg_keys.empty() || longest_row > kMinRowKeys);
     const int64_t target_waves = int64_t(num_cus) * kRowWavesPerCu;
     // The sequences with the fewest private keys, up to kTailWork of the row
     // work, get half-length items: ordered longest first, those run last, so
@@ -427,8 +469,6 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
       const int64_t L = seq_lens[r], len = L - kstart[r];
       const int64_t most = cdiv(L, kMinRowKeys) + (L > pa::kSharedMinKeys ? cdiv(L, pa::kSharedChunk) : 0) -
                            (cgroup[r] >= 0 ? cg_chunks[cgroup[r]] : 0);
-      // an item of up to 512 keys that needs no merge is not split into two that do
-      if (on_tiles(r) && cgroup[r] < 0 && len <= 2 * kMinTileKeys) return int64_t{1};
       return std::max<int64_t>(1, std::min(cdiv(len, on_tiles(r) ? tile_keys : row_chunk[r]), most));
     };
     for (int32_t S : cg_keys) cg_chunks.push_back(int32_t(cdiv(S, pa::kSharedChunk)));
@@ -453,7 +493,6 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
     // leaves it whole), a half leaves some that are (160 decode requests on 4096, 32/8
     // heads, 130 against 119).
     if (!cg_keys.empty()) {
-      constexpr double kStepBytes = 6.6e6, kStepFlops = 1.2e9;  // 1.2 us at 5.5 TB/s, 1 PFLOP/s
       double rest = 0;      // steps
       int64_t longest = 0;  // keys, in tile steps
       for (int32_t r = 0; r < n_seqs; ++r) {

@@ -134,9 +134,10 @@ def test_prefix_chunks_beside_enough_other_work_stay_whole():
 def test_few_row_tiles_fill_idle_compute_units():
     """33 to 64 rows per sequence: a launch that leaves compute units idle gets more
     items, one per compute unit at most; one key range of up to 512 keys that needs
-    no merge stays whole, and so does everything once the sequences fill the chip."""
+    no merge stays whole, and so does everything once the sequences fill the chip or
+    too few of them could be split to pay for the merge."""
     for n, own, hkv, prefix, more in [(1, 512, 8, 0, False), (1, 513, 8, 0, True), (1, 9000, 8, 0, True),
-                                      (5, 3000, 4, 768, True), (16, 700, 8, 0, True), (31, 700, 8, 0, True),
+                                      (5, 3000, 4, 768, True), (16, 700, 8, 0, True), (31, 700, 8, 0, False),
                                       (32, 4100, 8, 4096, False), (33, 4100, 8, 0, False)]:
         L = np.full(n, prefix + own)
         L[1:] -= own // 3
@@ -199,3 +200,27 @@ def test_float32_short_sequences_of_one_row_run_by_row():
         assert (info.variant == 16) == by_row
         if by_row:
             assert info.grid == sum(q) * hq
+
+
+def test_few_row_tiles_beside_longer_work_stay_whole():
+    """Items whose keys take less than half of what the row items take are not split;
+    longer ones are."""
+    for own, decodes, more in [(1300, 8, True), (1300, 256, False), (7000, 256, True)]:
+        q = np.array([12] + [1] * decodes)
+        L = np.array([own] + [1024 + 704] * decodes)
+        cu = np.concatenate([[0], np.cumsum(q)])
+        bt = _tables(None, np.concatenate([L[1:], L[:1]]), 1024)
+        bt = np.concatenate([bt[-1:], bt[:-1]])
+        bt[0, :64] += 5 * 10 ** 7
+        plan, info = B.plan(B.KIND_PREFILL, 0, L, cu, 32, 8, 128, 16, B.PA_BF16, 256, block_table=bt)
+        check_plan(plan, info, L, cu, 4, 8, 128)
+        assert (info.n_tile_items > 8 * -(-own // 4160)) == more
+
+
+def test_few_row_tiles_are_split_together():
+    """Where the longest sequences are split, so are the others that hold two parts: an
+    item left whole would be what the launch waits for."""
+    L = np.array([700] + [467] * 3)
+    plan, info = B.plan(B.KIND_VERIFY, 5, L, np.arange(5) * 5, 64, 8, 128, 16, B.PA_BF16, 256)
+    check_plan(plan, info, L, np.arange(5) * 5, 8, 8, 128)
+    assert max(t[5] - t[4] for t in parse_plan(plan)[2]) <= 256
