@@ -224,3 +224,16 @@ def test_few_row_tiles_are_split_together():
     plan, info = B.plan(B.KIND_VERIFY, 5, L, np.arange(5) * 5, 64, 8, 128, 16, B.PA_BF16, 256)
     check_plan(plan, info, L, np.arange(5) * 5, 8, 8, 128)
     assert max(t[5] - t[4] for t in parse_plan(plan)[2]) <= 256
+
+
+def test_tiles_beside_longer_row_work_stay_whole():
+    """One prefill chunk's tiles are split beside few decode requests, and whole beside
+    so many that their row items take twice as long."""
+    for hq, hkv, decodes, more in [(32, 8, 8, True), (32, 8, 64, True), (28, 4, 256, True), (32, 8, 256, False),
+                                   (32, 8, 512, False)]:
+        q = np.array([512] + [1] * decodes)
+        L = np.array([2560] + [2048 + 704] * decodes)
+        cu = np.concatenate([[0], np.cumsum(q)])
+        plan, info = B.plan(B.KIND_PREFILL, 0, L, cu, hq, hkv, 128, 16, B.PA_BF16, 256, block_table=_tables(None, L, 2048))
+        check_plan(plan, info, L, cu, hq // hkv, hkv, 128)
+        assert (info.n_tile_items > 512 * hq // 128) == more
