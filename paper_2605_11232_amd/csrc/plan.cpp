@@ -52,15 +52,15 @@ constexpr int64_t kPrivateTileKeys = 4160;  // most private keys a few-row tile 
 constexpr int64_t kMinTileKeys = 256;       // fewest, in launches that leave compute units idle
 constexpr int64_t kMinRowKeys = 256;        // split target floor of row items
 // Fewest keys a row item is split down to in a launch without long sequences'
-// tiles (beside those the rows are not what it waits for) that comes to at most
-// kSmallRowWavesPerCu such items per CU, while the sequence's part count stays
-// within the workspace bound: 4 decode requests on a 2048-token prefix 19.4 us per
+// tiles (beside those the rows are not what it waits for) that comes to at most 3
+// such items per CU (6 at head_dim 64, where they are half as long), while the
+// sequence's part count stays within the workspace bound: 4 decode requests on a 2048-token prefix 19.4 us per
 // append and call against 20.7 with 256 (128: even).  More of them no longer find a
 // compute unit each and only cost more parts: 48 requests of 460-1536 keys past 512
 // shared ones, 28/4 heads (1088 items against 896) 24.6 us and 21.5, 93 of them past
-// 992 43.2 and 40.1, 48 of 32/8 heads 41.0 and 37.3.
+// 992 43.2 and 40.1, 48 of 32/8 heads 41.0 and 37.3; at head_dim 64, 64 of 240-800
+// past 2048 (1390 items) 17.9 and 19.1, 128 past 992 (2770) 32.0 and 30.7.
 constexpr int64_t kSmallRowKeys = 192;
-constexpr int64_t kSmallRowWavesPerCu = 3;
 // What the whole chip does during one 64-key step of a tile: 1.2 us at 5.5 TB/s,
 // 1 PFLOP/s.
 constexpr double kStepBytes = 6.6e6, kStepFlops = 1.2e9;
@@ -478,7 +478,7 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
     };
     for (int32_t S : cg_keys) cg_chunks.push_back(int32_t(cdiv(S, pa::kSharedChunk)));
     const bool small_rows =
-        !long_seqs && cdiv(row_keys, kSmallRowKeys) <= kSmallRowWavesPerCu * num_cus;
+        !long_seqs && cdiv(row_keys, kSmallRowKeys) <= (head_dim == 64 ? 6 : 3) * int64_t(num_cus);
     split_rows(small_rows ? kSmallRowKeys : kMinRowKeys);
 
     // Key chunks of the shared prefixes.  A shared item is a serial walk over
@@ -506,9 +506,10 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
         if (is_row(r)) {
           rest += double(keys) * num_kv_heads * head_dim * 4 / kStepBytes;
           int64_t per = cdiv(keys, private_parts(r));
-          // rows of the usual length as of the small launches' (992 shared keys in two
-          // chunks beside them: 64 requests of 240-800 keys, 32/8 heads, 29 us and 34)
-          if (!on_tiles(r)) per = 2 * (per <= kMinRowKeys ? std::min(per, kSmallRowKeys) : per);
+          // without long sequences' tiles, rows of the usual length as of the small
+          // launches' (992 shared keys in two chunks beside them: 64 requests of 240-800
+          // keys, 32/8 heads, 29 us and 34)
+          if (!on_tiles(r)) per = 2 * (!long_seqs && per <= kMinRowKeys ? std::min(per, kSmallRowKeys) : per);
           longest = std::max(longest, per);
         } else {
           rest += 4.0 * head_dim * qlen(r) * num_q_heads * double(keys) / kStepFlops;

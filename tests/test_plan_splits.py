@@ -106,12 +106,13 @@ def test_decode_plans_of_many_heads_fit_the_array_without_workspace(D):
 
 
 def test_row_items_are_split_finer_only_where_they_leave_the_chip_room():
-    """Row items of 192 keys up to 3 of them per compute unit, beyond that of 256
-    (769 private keys: five parts of 160, or four of 224)."""
-    for n, hkv, most in [(4, 8, 160), (23, 8, 160), (25, 8, 224), (46, 4, 160), (50, 4, 224)]:
+    """Row items of 192 keys up to 3 of them per compute unit (6 at head_dim 64), beyond
+    that of 256 (769 private keys: five parts of 160, or four of 224)."""
+    for n, hkv, D, most in [(4, 8, 128, 160), (23, 8, 128, 160), (25, 8, 128, 224), (46, 4, 128, 160),
+                            (50, 4, 128, 224), (46, 8, 64, 160), (50, 8, 64, 224)]:
         L = np.full(n, 960 + 769)
         bt = _tables(None, L, 960)
-        plan, info = B.plan(B.KIND_DECODE, 1, L, np.arange(n + 1), 4 * hkv, hkv, 128, 16, B.PA_BF16, 256, block_table=bt)
+        plan, info = B.plan(B.KIND_DECODE, 1, L, np.arange(n + 1), 4 * hkv, hkv, D, 16, B.PA_BF16, 256, block_table=bt)
         assert max(t[5] - t[4] for t in parse_plan(plan)[3] if t[0] >= 0) == most
 
 
