@@ -469,17 +469,25 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
         if (cdiv(len, half) <= cdiv(seq_lens[r], kMinRowKeys)) row_chunk[r] = half;
       }
     };
-    // private parts of a sequence, within the workspace bound's part count
-    auto private_parts = [&](int32_t r) {
+    // private parts of a sequence, within the workspace bound's part count; n_private
+    // holds those of the few-row sequences
+    std::vector<int32_t> n_private(n_seqs, 0);
+    auto count_private = [&](int32_t r) {
       const int64_t L = seq_lens[r], len = L - kstart[r];
       const int64_t most = cdiv(L, kMinRowKeys) + (L > pa::kSharedMinKeys ? cdiv(L, pa::kSharedChunk) : 0) -
                            (cgroup[r] >= 0 ? cg_chunks[cgroup[r]] : 0);
-      return std::max<int64_t>(1, std::min(cdiv(len, on_tiles(r) ? tile_keys : row_chunk[r]), most));
+      n_private[r] =
+          int32_t(std::max<int64_t>(1, std::min(cdiv(len, on_tiles(r) ? tile_keys : row_chunk[r]), most)));
+    };
+    auto count_all_private = [&] {
+      for (int32_t r = 0; r < n_seqs; ++r)
+        if (is_row(r)) count_private(r);
     };
     for (int32_t S : cg_keys) cg_chunks.push_back(int32_t(cdiv(S, pa::kSharedChunk)));
     const bool small_rows =
         !long_seqs && cdiv(row_keys, kSmallRowKeys) <= (head_dim == 64 ? 6 : 3) * int64_t(num_cus);
     split_rows(small_rows ? kSmallRowKeys : kMinRowKeys);
+    count_all_private();
 
     // Key chunks of the shared prefixes.  A shared item is a serial walk over
     // its keys, so in a launch with little else to do few long chunks leave
@@ -505,7 +513,7 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
         const int64_t keys = seq_lens[r] - kstart[r];
         if (is_row(r)) {
           rest += double(keys) * num_kv_heads * head_dim * 4 / kStepBytes;
-          int64_t per = cdiv(keys, private_parts(r));
+          int64_t per = cdiv(keys, n_private[r]);
           // without long sequences' tiles, rows of the usual length as of the small
           // launches' (992 shared keys in two chunks beside them: 64 requests of 240-800
           // keys, 32/8 heads, 29 us and 34)
@@ -525,7 +533,9 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
       for (size_t c = 0; c < cg_keys.size(); ++c) {
         const int64_t n = std::min<int64_t>({cg_keys[c] / longest, (cg_keys[c] + share / 2) / share,
                                              num_cus / (row_tiles * num_kv_heads)});
-        cg_chunks[c] = int32_t(std::max<int64_t>(cg_chunks[c], n));
+        if (n <= cg_chunks[c]) continue;
+        cg_chunks[c] = int32_t(n);
+        for (int32_t m = cg_begin[c]; m < cg_begin[c + 1]; ++m) count_private(cg_seqs[m]);
       }
     }
     // A decode plan that fits pa_attn_decode_noalloc's array with the coarser
@@ -533,10 +543,11 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
     if (kind == PA_KIND_DECODE) {
       int64_t parts = 0;  // times G rows, per kv-head
       for (int32_t r = 0; r < n_seqs; ++r)
-        parts += private_parts(r) + (cgroup[r] >= 0 ? cg_chunks[cgroup[r]] : 0);
+        parts += n_private[r] + (cgroup[r] >= 0 ? cg_chunks[cgroup[r]] : 0);
       if (parts * num_q_heads * (head_dim + 1) * 4 > int64_t(PA_NOALLOC_WORKSPACE_BYTES)) {
         for (size_t c = 0; c < cg_keys.size(); ++c) cg_chunks[c] = int32_t(cdiv(cg_keys[c], pa::kSharedChunk));
         split_rows(kMinRowKeys);
+        count_all_private();
       }
     }
     // Decode of more than 64 heads per kv-head runs on these tiles, and whole
@@ -554,10 +565,8 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
       for (int32_t r = 0; r < n_seqs; ++r) {
         if (qlen(r) == 0) continue;
         if (is_row(r)) ng += cdiv(qlen(r) * G, pa::kMergeRows);
-        if (is_row(r) && on_tiles(r))
-          nt += private_parts(r);
-        else if (is_row(r))
-          nr += private_parts(r);
+        if (is_row(r))
+          (on_tiles(r) ? nt : nr) += n_private[r];
         else
           nt += cdiv(int64_t(qlen(r)) * G, pa::kTileRows);
       }
@@ -578,7 +587,7 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
         const int64_t kstep = tiled ? pa::kTileStep : pa::kKeyStep;
         // parts 0 .. first-1 are the shared prefix's key chunks
         const int32_t first = cgroup[r] >= 0 ? cg_chunks[cgroup[r]] : 0;
-        const int32_t nsplit = static_cast<int32_t>(private_parts(r));
+        const int32_t nsplit = n_private[r];
         // equal private key ranges, multiples of the key step, covering [k0s, L)
         const int64_t per = cdiv(cdiv(L - k0s, nsplit), kstep) * kstep;
         int32_t used = 0;
