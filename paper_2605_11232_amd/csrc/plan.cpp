@@ -439,7 +439,7 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
     // chunks and items of such launches are pinned by their tests (4 verifications of 5
     // tokens on 16384 shared and 4096 private keys: 3 chunks, one private item each, 101
     // us; splitting both would take 41).
-    const int64_t tile_keys =
+    int64_t tile_keys =
         longest_prefix > pa::kSharedChunk
             ? kPrivateTileKeys
             : few_tile_keys(few, num_kv_heads, head_dim, num_cus, num_cus - long_tiles, row_steps,
@@ -547,6 +547,7 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
       if (parts * num_q_heads * (head_dim + 1) * 4 > int64_t(PA_NOALLOC_WORKSPACE_BYTES)) {
         for (size_t c = 0; c < cg_keys.size(); ++c) cg_chunks[c] = int32_t(cdiv(cg_keys[c], pa::kSharedChunk));
         split_rows(kMinRowKeys);
+        tile_keys = kPrivateTileKeys;
         count_all_private();
       }
     }

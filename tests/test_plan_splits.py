@@ -70,6 +70,9 @@ def test_decode_plans_keep_fitting_the_array_without_workspace():
                 assert info.workspace_bytes <= B.NOALLOC_WORKSPACE_BYTES
                 fits += 1
     assert fits > 5
+    # few-row tiles for a caller that names more compute units than there are
+    _, info = B.plan(B.KIND_DECODE, 1, [1 << 20], [0, 1], 64, 1, 128, 16, B.PA_BF16, 4096)
+    assert 0 < info.workspace_bytes <= B.NOALLOC_WORKSPACE_BYTES
 
 
 def test_plan_info_counts_merge_groups():
