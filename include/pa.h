@@ -44,7 +44,7 @@
  *  - A query at logical position a sees keys 0..a (causal, bottom-right).
  *  - Supported: block_size 16, head_dim 64 or 128, num_q_heads a multiple of
  *    num_kv_heads; dtype PA_BF16 (MFMA path, float32 accumulation) or PA_F32
- *    (float32 VALU path).  Integers are int32; num_blocks * block_size must
+ *    (float32 throughout).  Integers are int32; num_blocks * block_size must
  *    be below 2^31.
  *  - Not thread-safe per pool; device calls on one stream are ordered.
  */
@@ -394,10 +394,9 @@ int pa_stage_upload(void* dst, const void* src, int64_t bytes, void* stream);
  * that is 0.  Block ids must lie in [0, num_blocks); out-of-range ids are
  * clamped so no access leaves the cache (results are then undefined).
  * Every pointer is caller-owned device memory (info: host); the call
- * allocates nothing, writes only out, lse, the workspace and two counter
- * words of the plan's header, which its work-stealing workgroups count on
- * (device-scope atomics) and which it leaves zero, as pa_attn_plan wrote
- * them, so one device plan serves any number of calls ordered on a stream
+ * allocates nothing, writes only out, lse, the workspace and the counters
+ * in the plan, which its work-stealing workgroups count on (device-scope
+ * atomics) and which it leaves zero, as pa_attn_plan wrote them, so one device plan serves any number of calls ordered on a stream
  * (calls sharing one device plan must not overlap in time), and is
  * asynchronous on stream.  The three entry points differ only in the plan
  * kind they accept.

@@ -4,7 +4,8 @@
 // every row of an item reads the same keys and values (grouped-query
 // attention).  Sequences with many rows (suffix prefill, prefill chunks) are
 // cut into 128-row tile items, each a workgroup of four wavefronts sharing
-// key/value tiles through LDS.  Sequences with at most 32 rows (decode: G
+// key/value tiles through LDS; where a launch has few of them their key ranges
+// are split.  Sequences with at most 32 rows (decode: G
 // rows; short verification: n_q * G rows) become single-wavefront row items
 // whose key range is split so the launch has enough wavefronts in flight to
 // stream the cache at HBM bandwidth; sequences with 33..64 rows run their
@@ -54,12 +55,13 @@ constexpr int64_t kMinRowKeys = 256;        // split target floor of row items
 // Fewest keys a row item is split down to in a launch without long sequences'
 // tiles (beside those the rows are not what it waits for) that comes to at most 3
 // such items per CU (6 at head_dim 64, where they are half as long), while the
-// sequence's part count stays within the workspace bound: 4 decode requests on a 2048-token prefix 19.4 us per
-// append and call against 20.7 with 256 (128: even).  More of them no longer find a
-// compute unit each and only cost more parts: 48 requests of 460-1536 keys past 512
-// shared ones, 28/4 heads (1088 items against 896) 24.6 us and 21.5, 93 of them past
-// 992 43.2 and 40.1, 48 of 32/8 heads 41.0 and 37.3; at head_dim 64, 64 of 240-800
-// past 2048 (1390 items) 17.9 and 19.1, 128 past 992 (2770) 32.0 and 30.7.
+// sequence's part count stays within the workspace bound: 4 decode requests on a
+// 2048-token prefix 19.4 us per append and call against 20.7 with 256 (128: even).
+// More of them no longer find a compute unit each and only cost more parts: 48
+// requests of 460-1536 keys past 512 shared ones, 28/4 heads (1088 items against 896)
+// 24.6 us and 21.5, 93 of them past 992 43.2 and 40.1, 48 of 32/8 heads 41.0 and 37.3;
+// at head_dim 64, 64 of 240-800 past 2048 (1390 items) 17.9 and 19.1, 128 past 992
+// (2770) 32.0 and 30.7.
 constexpr int64_t kSmallRowKeys = 192;
 // What the whole chip does during one 64-key step of a tile: 1.2 us at 5.5 TB/s,
 // 1 PFLOP/s.
@@ -280,9 +282,9 @@ int64_t few_tile_keys(const std::vector<FewTile>& few, int32_t hkv, int32_t head
 // of 64, one token each, 64 sequences of 40 keys 9.9 and 14.6, of 100 18.8 and
 // 22.0, of 150 25.7 and 28.8, 256 of 200-300 196 and 188; of 128, 64 of 64 keys 24
 // and 29, 128 of 100 94 and 87; two tokens each, heads of 64, 400 of 40 keys 69 and
-// 89, of 64 115 and 105 (of 128, 40 keys 173 and 159); 32/16 heads of 128 (two rows), 400 of 16 keys 35 and 47, of
-// 40 91 and 79; 32/8 heads, 400 of 16 21 and 16; 16 sequences of 32/32 heads, 40
-// keys, 9.3 and 6.4.
+// 89, of 64 115 and 105 (of 128, 40 keys 173 and 159); 32/16 heads of 128 (two rows),
+// 400 of 16 keys 35 and 47, of 40 91 and 79; 32/8 heads, 400 of 16 21 and 16; 16
+// sequences of 32/32 heads, 40 keys, 9.3 and 6.4.
 bool f32_by_row(int32_t n_seqs, const int32_t* seq_lens, const int32_t* cu, int32_t hq, int32_t hkv,
                 int32_t head_dim, int32_t num_cus) {
   const int32_t G = hq / hkv;
@@ -653,7 +655,8 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
       const int64_t total_rows = int64_t(rpm) * nmem;
       const int32_t nch = cg_chunks[cg];
       // chunk boundaries on the tile step; every chunk is non-empty because
-      // S / nch >= kSharedChunk / 2 > kTileStep
+      // S / nch >= kSharedMinKeys > kTileStep (cg_chunks: at most S / longest, at least
+      // kSharedMinKeys, or cdiv(S, kSharedChunk))
       auto bound = [&](int64_t c) {
         return c >= nch ? int64_t(S) : (c * S / nch) / pa::kTileStep * pa::kTileStep;
       };
@@ -777,8 +780,8 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
     // take: the lists only cost it round trips to the counters (116 tiles of 12-34
     // tokens 14.1 us per append and call with them, 11.4 without; 64 tiles 13.5 and
     // 11.0).  Up to two workgroups per CU start at once and would gain the same 2 us;
-    // the line is at one on every other CU because plans above it (192 workgroups)
-    // are relied on to have lists.
+    // the line is at one on every other CU only because the tests of the lists run
+    // launches just above it (192 workgroups).
     if (kStealPct > 0 && !split_keys && 2 * int64_t(dispatch.size()) > num_cus) {
       const int32_t t_lo = int32_t(t_shared.size()), t_hi = t_lo + int32_t(t_tiles.size());
       auto stealable = [&](const Ref& r) {
@@ -926,13 +929,16 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
 }
 
 // Workspace bound.  A sequence with split keys writes one partial row per
-// (query row, part); its parts are its private key ranges (at least
-// kMinRowKeys keys each, kPrivateTileKeys for tile-run private parts) plus
-// its shared prefix's key chunks (at least kSharedChunk / 2 keys each, and
-// never more than cdiv(shared keys, kSharedChunk)).  Both counts grow with
-// the key count, so a sequence of at most L keys has at most
-// cdiv(L, kMinRowKeys) + cdiv(L, kSharedChunk) parts (no shared chunk when
-// L <= kSharedMinKeys), and a query token has num_q_heads rows.
+// (query row, part).  A sequence of at most L keys has at most
+// cdiv(L, kMinRowKeys) + cdiv(L, kSharedChunk) parts (the latter not when
+// L <= kSharedMinKeys): its prefix has at most max(cdiv(S, kSharedChunk),
+// S / kSharedMinKeys) chunks of S < L shared keys, and count_private leaves its
+// private ranges, however short they may be, no more than what the chunks leave
+// of that number (at least one).  A key-split tile's rows have at most
+// cdiv(L, kSplitKeys) parts, and kSplitKeys is kMinRowKeys.  Plans rely on both
+// and not on the lengths of the parts.  A query token has num_q_heads rows.
+static_assert(kSplitKeys >= kMinRowKeys && pa::kSharedMinKeys >= kMinRowKeys,
+              "the workspace bound's part count");
 namespace {
 int workspace_bound(const char* fn, int32_t total_q, int32_t num_q_heads, int32_t head_dim,
                     int32_t max_seq_len, size_t* bytes) {

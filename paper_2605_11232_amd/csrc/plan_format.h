@@ -122,7 +122,7 @@ constexpr int32_t kVariantF32ByRow = 16;
 
 constexpr int32_t kTileRows = 128;    // rows per tile item (4 waves x 32)
 constexpr int32_t kRowItemRows = 32;  // rows per single-wave item (two 16-column MFMA tiles)
-constexpr int32_t kMergeRows = 4;     // rows per merge group (one wavefront each)
+constexpr int32_t kMergeRows = 4;     // rows per merge group (half a wavefront each)
 constexpr int32_t kWideGroupParts = kTileRows / kMergeRows;  // merge workgroups of a wide group
 constexpr int32_t kRowSeqRows = 64;   // sequences with at most this many rows use row items
 constexpr int32_t kKeyStep = 32;      // keys per row-item inner iteration

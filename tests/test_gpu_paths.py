@@ -203,6 +203,7 @@ def test_tile_rows_without_a_finite_first_score(d):
 def test_calls_use_the_current_stream():
     """A call without a stream argument goes to the stream torch has as current on the
     current device, whichever it is, and an explicit one to itself."""
+    _gpu()
     assert B._stream(None) == torch.cuda.current_stream().cuda_stream
     side = torch.cuda.Stream()
     with torch.cuda.stream(side):
