@@ -305,10 +305,10 @@ void launch_t(hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop, const
 
 // One wavefront per (query token, q-head), on vector instructions: a 64-key
 // chunk puts one key in each lane for the scores (16-byte loads of the key's
-// 32-dim runs, four partial sums), then the lanes switch to owning head
+// 32-dim runs, eight partial sums), then the lanes switch to owning head
 // dimensions for the weighted value sum: each lane reads one dimension's 16
 // offsets of a block as four 16-byte loads and takes the probabilities from
-// LDS, keys in order.  A workgroup of the tile kernel costs about as much for
+// LDS, in four partial sums.  A workgroup of the tile kernel costs about as much for
 // one row as for sixteen, and a chain of loads before its first key; where
 // sequences have one row or two and few keys, that is most of it.  The planner
 // chooses (f32_by_row).
@@ -340,9 +340,11 @@ __global__ __launch_bounds__(64) void attn_f32_row_kernel(
   for (int d = lane; d < D; d += 64) qsh[d] = q[((int64_t)token * hq + h) * D + d];
   __syncthreads();
 
-  float od[DL];
+  float od[DL][4];  // sums over every fourth key
 #pragma unroll
-  for (int k = 0; k < DL; ++k) od[k] = 0.f;
+  for (int k = 0; k < DL; ++k)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) od[k][e] = 0.f;
   float m = kNegInf, l = 0.f;
   for (int c0 = 0; c0 <= a; c0 += 64) {
     const int key = c0 + lane;
@@ -354,7 +356,7 @@ __global__ __launch_bounds__(64) void attn_f32_row_kernel(
     if (vis) {
       // the key's 32-dim runs in the grouped key layout, 32 floats each
       const float* kp = kc + ((int64_t)blk * hkv + g) * kBlock * D + key_elem(key % kBlock, 0);
-      float acc[4] = {0.f, 0.f, 0.f, 0.f};
+      float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int gd = 0; gd < D; gd += kKeyGroup) {
         const f32x4* k4 = reinterpret_cast<const f32x4*>(kp + gd * kBlock);
@@ -362,10 +364,10 @@ __global__ __launch_bounds__(64) void attn_f32_row_kernel(
         for (int j = 0; j < kKeyGroup / 4; ++j) {
           const f32x4 kv = k4[j];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) acc[j % 4] = fmaf(qsh[gd + 4 * j + e], kv[e], acc[j % 4]);
+          for (int e = 0; e < 4; ++e) acc[j % 8] = fmaf(qsh[gd + 4 * j + e], kv[e], acc[j % 8]);
         }
       }
-      s = ((acc[0] + acc[1]) + (acc[2] + acc[3])) * scale;
+      s = (((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]))) * scale;
     }
     float cm = s;
 #pragma unroll
@@ -379,7 +381,9 @@ __global__ __launch_bounds__(64) void attn_f32_row_kernel(
     l = l * alpha + ps;
     m = mnew;
 #pragma unroll
-    for (int k = 0; k < DL; ++k) od[k] *= alpha;
+    for (int k = 0; k < DL; ++k)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) od[k][e] *= alpha;
     psh[lane] = p;
     if (lane % kBlock == 0) bsh[lane / kBlock] = blk;
     __syncthreads();
@@ -396,12 +400,12 @@ __global__ __launch_bounds__(64) void attn_f32_row_kernel(
         for (int j = 0; j < kBlock / 4; ++j) vv[j] = v4[j];
         if (nb == kBlock) {
 #pragma unroll
-          for (int j = 0; j < kBlock; ++j) od[k] = fmaf(psh[kb + j], vv[j / 4][j % 4], od[k]);
+          for (int j = 0; j < kBlock; ++j) od[k][j % 4] = fmaf(psh[kb + j], vv[j / 4][j % 4], od[k][j % 4]);
         } else {
           // keys past the last visible one: slots that may never have been written
 #pragma unroll
           for (int j = 0; j < kBlock; ++j)
-            if (j < nb) od[k] = fmaf(psh[kb + j], vv[j / 4][j % 4], od[k]);
+            if (j < nb) od[k][j % 4] = fmaf(psh[kb + j], vv[j / 4][j % 4], od[k][j % 4]);
         }
       }
     }
@@ -409,7 +413,8 @@ __global__ __launch_bounds__(64) void attn_f32_row_kernel(
   }
   const float inv = 1.f / l;
 #pragma unroll
-  for (int k = 0; k < DL; ++k) out[((int64_t)token * hq + h) * D + lane + 64 * k] = od[k] * inv;
+  for (int k = 0; k < DL; ++k)
+    out[((int64_t)token * hq + h) * D + lane + 64 * k] = ((od[k][0] + od[k][1]) + (od[k][2] + od[k][3])) * inv;
   if (lse && lane == 0) lse[(int64_t)token * hq + h] = m + logf(l);
 }
 
