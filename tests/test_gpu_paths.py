@@ -200,6 +200,38 @@ def test_tile_rows_without_a_finite_first_score(d):
     close(p.lse.cpu().numpy(), lse.cpu().numpy(), *LSE_TOL["bf16"], cfg.name + " lse")
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_tile_values_near_the_largest_stay_finite(d):
+    """A key whose probability lies 2^11 above the first step's, with values of 3e35: the row's
+    output is finite, as the reference moves before the product leaves float32."""
+    _gpu()
+    from paper_2605_11232_amd.runtime import DeviceReplay
+    cfg = synth.AttnConfig(f"large-{d}", "bf16", 4, 2, d, 16, 6700 + d)
+    n, L, at = 130, 500, 300
+    dev = DeviceReplay(launch_workload(cfg, [n], [L], 92)).setup()
+    p = dev.prepare(dev.wl.launches[0])
+    dev.append(p)
+    bt = p.block_table[0].long()
+    t = torch.arange(L, device="cuda")
+    off = t % 16
+    pos = (off & ~12) | ((off & 4) << 1) | ((off & 8) >> 1)
+    # every score 0 (dim 0 of the queries is 8, the other dims of the keys 0) but one
+    p.q[:, :, 0] = 8.0
+    dev.k_cache[bt[t // 16], :, :, pos] = 0
+    score = 11 * 0.6931
+    dev.k_cache[bt[at // 16], :, 0, pos[at], 0] = score * d ** 0.5 / 8
+    dev.v_cache[bt[t // 16], :, :, off] = 0
+    dev.v_cache[bt[at // 16], :, :, off[at]] = 3e35
+    dev.attend(p)
+    torch.cuda.synchronize()
+    w = float(dev.k_cache[bt[at // 16], 0, 0, pos[at], 0].double()) * 8 * d ** -0.5
+    seen = (L - n + torch.arange(n, device="cuda") + 1).double()
+    v = float(dev.v_cache[bt[at // 16], 0, 0, off[at]].double())
+    ref = np.exp(w) * v / (np.exp(w) + seen - 1).cpu().numpy()
+    ref = np.where((seen > at).cpu().numpy(), ref, 0.0)[:, None, None] * np.ones((1, 4, d))
+    close(p.out.float().cpu().numpy() / v, ref / v, *TOL["bf16"], cfg.name)
+
+
 def test_calls_use_the_current_stream():
     """A call without a stream argument goes to the stream torch has as current on the
     current device, whichever it is, and an explicit one to itself."""
