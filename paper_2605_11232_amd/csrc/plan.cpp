@@ -175,12 +175,15 @@ void interleave(std::vector<U>& out, const std::vector<std::vector<U>>& queues) 
 // every other CU, as some get two; whole tiles 1.2, beyond one per CU, where causal
 // lengths differ and end apart, 1.4; at head_dim 64 about two thirds of that; the
 // merge takes 4 plus the parts at 4.5 TB/s; and a split has to save 15 %.  More than
-// two workgroups per CU are never made, nor parts of more than most_bytes.  Beside
-// row items that take at least twice as long as the longest whole tile (row_steps, in
-// steps of the whole chip) nothing waits for the tiles: one 512-token chunk on 2048
-// cached tokens (40 steps) beside 512 decode requests, 32/8 heads (222), 279 us whole
-// and 307 split; beside 256 (111) 168 and 170; beside 256 of 28/4 heads (55) 113 and
-// 101, beside 64 of 32/8 (28) 80 and 67.
+// two workgroups per CU are never made, nor parts of more than most_bytes.  Nothing
+// waits for the tiles beside other items that walk as many keys in series
+// (other_steps: 11 sequences of 26-41 tokens beside 85 of one token on 1056-3235 keys,
+// 96/2 heads of 64, 53 us whole and 71 split; 3 of 9-10 tokens among 74 sequences of
+// 4284-9418 keys, 64/8 heads, 263 and 318), nor in a launch that reads its keys for twice
+// as long as the longest whole tile takes (launch_steps, of the whole chip): one 512-token
+// chunk on 2048 cached tokens (40 steps) beside 512 decode requests, 32/8 heads (222), 279
+// us whole and 307 split; beside 256 (111) 168 and 170; beside 256 of 28/4 heads (56) 113
+// and 101, beside 64 of 32/8 (28) 80 and 67.
 // Append and call, 32/8 heads of 128: 389 new tokens of one request on 2048
 // cached ones (104 workgroups) 52.5 us whole, 39.7 in two parts, 35.9 in four;
 // 100 on 4096 (32) 83 and 26; 17-57 on 631 (16) 22 and 17; head_dim 64, two requests of
@@ -191,7 +194,7 @@ void interleave(std::vector<U>& out, const std::vector<std::vector<U>>& queues) 
 template <class IsRow>
 int64_t tile_split_keys(int32_t n_seqs, const int32_t* seq_lens, const int32_t* cu, int32_t G,
                         int32_t hkv, int32_t head_dim, int32_t num_cus, int64_t most_bytes,
-                        double row_steps, IsRow is_row) {
+                        int64_t other_steps, double launch_steps, IsRow is_row) {
   std::vector<int64_t> kv, tile_rows;  // keys and rows of each tile (of one kv-head)
   int64_t rows = 0, longest = 0;
   for (int32_t r = 0; r < n_seqs; ++r) {
@@ -206,8 +209,8 @@ int64_t tile_split_keys(int32_t n_seqs, const int32_t* seq_lens, const int32_t* 
     }
     rows += n * G * hkv;
   }
-  auto steps = [](int64_t keys) { return double(cdiv(keys, pa::kTileStep)); };
-  if (longest <= kSplitKeys || 2 * steps(longest) <= row_steps) return 0;
+  auto steps = [&](int64_t keys) { return double(std::max(cdiv(keys, pa::kTileStep), other_steps)); };
+  if (longest <= kSplitKeys || 2 * double(cdiv(longest, pa::kTileStep)) <= launch_steps) return 0;
   const double half_dim = head_dim == 64 ? 0.65 : 1;
   double best = 0.85 * steps(longest) * (int64_t(kv.size()) * hkv <= num_cus ? 1.2 * half_dim : 1.4);
   int64_t best_keys = 0;
@@ -555,9 +558,22 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
     }
     // Decode of more than 64 heads per kv-head runs on these tiles, and whole
     // they need no workspace: such a plan fits the same array.
+    int64_t other_steps = 0;  // of the longest other private item (a row item's step: 32 keys)
+    double launch_steps = 0;  // time of all private keys, in steps of the whole chip
+    if (long_seqs) {
+      for (int32_t r = 0; r < n_seqs; ++r) {
+        if (qlen(r) == 0) continue;
+        const int64_t keys = seq_lens[r] - kstart[r];
+        launch_steps += double(keys) * num_kv_heads * head_dim * 4 / kStepBytes;
+        if (is_row(r))
+          other_steps = std::max(other_steps, cdiv(cdiv(keys, n_private[r]),
+                                                   on_tiles(r) ? pa::kTileStep : pa::kKeyStep));
+      }
+    }
     const int64_t split_keys = tile_split_keys(
         n_seqs, seq_lens, cu_seqlens_q, G, num_kv_heads, head_dim, num_cus,
-        kind == PA_KIND_DECODE ? int64_t(PA_NOALLOC_WORKSPACE_BYTES) : INT64_MAX, row_steps, is_row);
+        kind == PA_KIND_DECODE ? int64_t(PA_NOALLOC_WORKSPACE_BYTES) : INT64_MAX, other_steps,
+        launch_steps, is_row);
 
     std::vector<int64_t> tile_cost, row_cost, shared_cost;
     // head-0 partial base of a cascade member's merge group

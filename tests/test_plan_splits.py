@@ -241,3 +241,14 @@ def test_tiles_beside_longer_row_work_stay_whole():
         plan, info = B.plan(B.KIND_PREFILL, 0, L, cu, hq, hkv, 128, 16, B.PA_BF16, 256, block_table=_tables(None, L, 2048))
         check_plan(plan, info, L, cu, hq // hkv, hkv, 128)
         assert (info.n_tile_items > 512 * hq // 128) == more
+
+
+def test_tiles_beside_other_long_items_stay_whole():
+    """Splitting a long sequence's tiles gains nothing while few-row items walk as many
+    keys in series."""
+    q = np.array([1] * 85 + [30] * 11)
+    L = np.linspace(1056, 3235, 96).astype(int)
+    cu = np.concatenate([[0], np.cumsum(q)])
+    plan, info = B.plan(B.KIND_PREFILL, 0, L, cu, 96, 2, 64, 16, B.PA_BF16, 256)
+    check_plan(plan, info, L, cu, 48, 2, 64)
+    assert info.workspace_bytes == 0
