@@ -237,9 +237,11 @@ int64_t tile_split_keys(int32_t n_seqs, const int32_t* seq_lens, const int32_t* 
 // kPrivateTileKeys.  An item walks its keys in series; the split pays where the
 // steps it saves take longer than the merge it needs (unless the launch has one),
 // and not beside row items that take twice as long as the longest item anyway (four
-// times where an XCD has several, as they start spread over the row items).  A
-// step takes about a microsecond (head_dim 64 two thirds), 5 % more beyond one item
-// on every other CU, the merge 3.5 (2.7) plus the parts at 4.5 TB/s.
+// times where an XCD has several, as they start spread over the row items).  A range
+// of up to 512 keys that needs no merge is not split for itself (122 sequences of 1-17
+// tokens on 258-276 keys 19.7 us, 21.4 with the single ones of them split).  A step
+// takes about a microsecond (head_dim 64 two thirds), 5 % more beyond one item on every
+// other CU, the merge 3.5 (2.7) plus the parts at 4.5 TB/s.
 // Call, us, whole and split: one verification of 5 tokens on 900 keys, 64/8 heads, 20
 // and 12, four on 467-700 15.3 and 12.9, 16 of them even, 31 (248 items, where one
 // sequence alone could be split) 17.6 and 19.0; 27 decode requests of 180-600 keys,
@@ -248,6 +250,7 @@ int64_t tile_split_keys(int32_t n_seqs, const int32_t* seq_lens, const int32_t* 
 // 133 and 138, on 7000 172 and 149, four on 2000 159 and 149, on 300 139 and 141.
 struct FewTile {
   int64_t keys, rows;
+  bool merged;  // a cascade member: its rows are merged anyway
 };
 int64_t few_tile_keys(const std::vector<FewTile>& few, int32_t hkv, int32_t head_dim, int32_t num_cus,
                       int64_t free_cus, double row_steps, bool other_merge) {
@@ -256,10 +259,14 @@ int64_t few_tile_keys(const std::vector<FewTile>& few, int32_t hkv, int32_t head
     for (const auto& f : few) n += cdiv(f.keys, keys) * hkv;
     return n;
   };
-  int64_t longest = 0;
-  for (const auto& f : few) longest = std::max(longest, f.keys);
+  int64_t longest = 0, longest_merged = 0;
+  for (const auto& f : few) {
+    longest = std::max(longest, f.keys);
+    if (f.merged) longest_merged = std::max(longest_merged, f.keys);
+  }
   const double room = items(kPrivateTileKeys) > kXcds ? row_steps / 2 : row_steps;
-  if (items(kPrivateTileKeys) >= free_cus || (!other_merge && longest <= 2 * kMinTileKeys) ||
+  if (items(kPrivateTileKeys) >= free_cus ||
+      (longest <= 2 * kMinTileKeys && longest_merged <= kMinTileKeys) ||
       2 * double(cdiv(longest, pa::kTileStep)) <= room)
     return kPrivateTileKeys;
   auto estimate = [&](int64_t keys) {
@@ -432,7 +439,7 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
     for (int32_t r = 0; r < n_seqs; ++r) {
       const int64_t keys = seq_lens[r] - kstart[r];
       if (!is_row(r)) long_tiles += cdiv(int64_t(qlen(r)) * G, pa::kTileRows) * num_kv_heads;
-      else if (on_tiles(r)) few.push_back({keys, int64_t(qlen(r)) * G});
+      else if (on_tiles(r)) few.push_back({keys, int64_t(qlen(r)) * G, cgroup[r] >= 0});
       else row_keys += keys * num_kv_heads, longest_row = std::max(longest_row, keys);
     }
     const bool long_seqs = long_tiles > 0;
@@ -558,7 +565,7 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
     }
     // Decode of more than 64 heads per kv-head runs on these tiles, and whole
     // they need no workspace: such a plan fits the same array.
-    int64_t other_steps = 0;  // of the longest other private item (a row item's step: 32 keys)
+    int64_t other_steps = 0;  // of the longest other private item, in tile steps
     double launch_steps = 0;  // time of all private keys, in steps of the whole chip
     if (long_seqs) {
       for (int32_t r = 0; r < n_seqs; ++r) {
@@ -566,8 +573,7 @@ extern "C" int pa_attn_plan(int32_t kind, int32_t n_q, int32_t n_seqs, const int
         const int64_t keys = seq_lens[r] - kstart[r];
         launch_steps += double(keys) * num_kv_heads * head_dim * 4 / kStepBytes;
         if (is_row(r))
-          other_steps = std::max(other_steps, cdiv(cdiv(keys, n_private[r]),
-                                                   on_tiles(r) ? pa::kTileStep : pa::kKeyStep));
+          other_steps = std::max(other_steps, cdiv(cdiv(keys, n_private[r]), pa::kTileStep));
       }
     }
     const int64_t split_keys = tile_split_keys(

@@ -252,3 +252,14 @@ def test_tiles_beside_other_long_items_stay_whole():
     plan, info = B.plan(B.KIND_PREFILL, 0, L, cu, 96, 2, 64, 16, B.PA_BF16, 256)
     check_plan(plan, info, L, cu, 48, 2, 64)
     assert info.workspace_bytes == 0
+
+
+def test_short_few_row_sequences_stay_whole_beside_merged_ones():
+    """A sequence of up to 512 keys that needs no merge is not split because others of the
+    launch, members of a shared prefix with few keys of their own, have one."""
+    q = np.array([10] * 6 + [12])
+    L = np.array([266] * 6 + [300])
+    cu = np.concatenate([[0], np.cumsum(q)])
+    plan, info = B.plan(B.KIND_PREFILL, 0, L, cu, 32, 8, 128, 16, B.PA_BF16, 256, block_table=_tables(None, L, 256))
+    check_plan(plan, info, L, cu, 4, 8, 128)
+    assert info.n_shared_items > 0 and info.n_tile_items == 7 * 8
